@@ -460,12 +460,32 @@ int64_t next_tag(rs_table* t) {
   return t->tag;
 }
 
+void record_pair(hipEvent_t* ev, hipStream_t s) {
+  if (ev && ev[0]) (void)hipEventRecord(ev[0], s);
+  if (ev && ev[1]) (void)hipEventRecord(ev[1], s);
+}
+
 // Dedup `values` into w, then find-or-insert the unique keys (growing the
-// table first when it may not have room).
+// table first when it may not have room).  Without occ_lists rows_out [n] and
+// n_inserted (may be null) receive the rows and the number inserted.
 rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const Work& w, bool occ_lists,
-                           hipStream_t s) {
+                           int64_t* rows_out, int64_t* n_inserted, hipStream_t s) {
   rs_status st = RS_OK;
   const int64_t tag = next_tag(t);
+  if (n > 0 && small_batch(n)) {
+    // its front end reserves rows and inserts in one go: only where n new keys
+    // are known to fit
+    refresh_bound(t);
+    const int64_t after = t->live_bound + n;
+    if (after <= t->limit && after <= t->rows_prov) {
+      RS_HIP(launch_small_front(values, n, t->dev(), w, occ_lists, t->h_pin, tag, rows_out, n_inserted,
+                                t->ev(RS_K_TILE_DEDUP), t->ev(RS_K_COMPACT_INSERT), s));
+      for (int k : {RS_K_PARTITION, RS_K_INIT_ROWS, RS_K_OCC}) record_pair(t->ev(k), s);  // no launch of their own
+      t->live_bound = after;
+      t->bound_after[tag % rs_table::kTags] = after;
+      return RS_OK;
+    }
+  }
   RS_HIP(launch_dedup_probe(values, n, t->dev(), w, t->h_pin, tag, t->ev(RS_K_TILE_DEDUP), t->ev(RS_K_PARTITION), s));
   refresh_bound(t);
   const int64_t bound = t->live_bound + n;
@@ -505,6 +525,8 @@ rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const 
   }
   RS_HIP(launch_compact_insert(values, n, t->dev(), w, occ_lists, t->ev(RS_K_COMPACT_INSERT),
                                t->ev(RS_K_INIT_ROWS), t->ev(RS_K_OCC), s));
+  if (occ_lists && small_batch(n)) RS_HIP(launch_clear_refs(w, n, s));
+  if (!occ_lists) RS_HIP(launch_map_rows(w, n, rows_out, n_inserted, s));
   return RS_OK;
 }
 
@@ -789,10 +811,7 @@ rs_status ht_find_or_insert(rs_table* t, const int64_t* keys, int64_t n, int64_t
   }
   const Work w = make_work(t->iws, L);
   t->clock += 1;  // one lookup call
-  rs_status st = dedup_and_insert(t, keys, n, w, false, s);
-  if (st != RS_OK) return st;
-  RS_HIP(launch_map_rows(w, n, rows_out, n_inserted_dev, s));
-  return RS_OK;
+  return dedup_and_insert(t, keys, n, w, false, rows_out, n_inserted_dev, s);
 }
 
 rs_status ht_find(rs_table* t, const int64_t* keys, int64_t n, int64_t* rows_out, rs_stream stream) {
@@ -990,7 +1009,7 @@ rs_status lookup_prepare(rs_table* t, const int64_t* values, const int64_t* offs
   ctx->mode = mode;
   ctx->dim = t->d.dim;
   t->clock += 1;  // one lookup call
-  rs_status st = dedup_and_insert(t, values, n, w, true, s);
+  rs_status st = dedup_and_insert(t, values, n, w, true, nullptr, nullptr, s);
   if (st != RS_OK) return st;
   ctx->priv[0] = 1;
   ctx->table = t;

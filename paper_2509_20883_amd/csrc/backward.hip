@@ -21,7 +21,9 @@
 //                     (no atomics)
 //   k_bwd_long_finish one block per hot key sums the partial rows of its
 //                     units in a fixed order and applies the optimizer
-// Without the optimizer (lookup_pool_bwd) the same kernels write grad_unique.
+// A small batch takes both strategies and the finish in one launch
+// (k_bwd_small).  Without the optimizer (lookup_pool_bwd) the same kernels
+// write grad_unique.
 #include "device_common.h"
 
 #include <hip/hip_ext.h>
@@ -355,62 +357,145 @@ __global__ __launch_bounds__(kBlock) void k_bwd_long(Work w, uint32_t nref, cons
   bwd_units<GT, LANES, MODE>(w, nref, grad, L, 8 * per);
 }
 
+// E values at p (8-byte aligned) that other blocks of the same launch read or
+// wrote: agent-scope accesses, which pass by the caches that are not coherent
+// between the XCDs.
+template <int E>
+__device__ inline void store_agent(float* p, const float (&v)[E]) {
+#pragma unroll
+  for (int k = 0; k < E; k += 2) {
+    const unsigned long long b = static_cast<unsigned long long>(__float_as_uint(v[k])) |
+                                 static_cast<unsigned long long>(__float_as_uint(v[k + 1])) << 32;
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p + k), b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+template <int E>
+__device__ inline void load_agent(const float* p, float (&v)[E]) {
+  unsigned long long b[E / 2];
+#pragma unroll
+  for (int k = 0; k < E / 2; ++k)
+    b[k] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p + 2 * k), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int k = 0; k < E; ++k) v[k] = __uint_as_float(static_cast<uint32_t>(b[k / 2] >> (32 * (k % 2))));
+}
+
+// Hot key li, by the whole block: its units' partial rows summed in a fixed
+// order (lane groups, then an LDS tree) and the optimizer (or grad_unique).
+// AGENT: the partial rows were written in this launch.
+template <typename WT, int E, int LANES, bool FUSED, bool AGENT>
+__device__ inline void finish_key(const TableDev& t, const Work& w, int64_t li, float* __restrict__ grad_unique,
+                                  const OptArgs& o, float (*red)[LANES * E]) {
+  constexpr int GPB = kBlock / LANES;
+  constexpr int D = LANES * E;
+  const int lane = threadIdx.x % LANES;
+  const int grp = threadIdx.x / LANES;
+  const int u = w.long_u[li];
+  const Seg sg = w.useg[u];
+  const int nu = unit_count(sg.count);
+  const int64_t u0 = w.long_start[li];
+  RowFrag<WT, E> fr;
+  uint8_t* rp = nullptr;
+  if (FUSED && grp == 0 && sg.row >= 0) {
+    rp = t.store.row(sg.row);
+    fr.load(rp, lane, D, t.nstate, t.rowscalar);  // in flight while the partial rows are read
+  }
+  float acc[E];
+#pragma unroll
+  for (int q = 0; q < E; ++q) acc[q] = 0.f;
+  for (int j = grp; j < nu; j += 2 * GPB) {
+    float x[E], y[E];
+    const float* const px = w.gpart + (u0 + j) * D + lane * E;
+    const float* const py = px + GPB * D;
+    const bool two = j + GPB < nu;
+    if (AGENT) {
+      load_agent<E>(px, x);
+      if (two) load_agent<E>(py, y);
+    } else {
+      load_vals<float, E>(px, x);
+      if (two) load_vals<float, E>(py, y);
+    }
+#pragma unroll
+    for (int q = 0; q < E; ++q) acc[q] += x[q];
+    if (two) {
+#pragma unroll
+      for (int q = 0; q < E; ++q) acc[q] += y[q];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < E; ++q) red[grp][lane * E + q] = acc[q];
+  __syncthreads();
+  for (int h = GPB / 2; h >= 1; h >>= 1) {
+    if (grp < h) {
+#pragma unroll
+      for (int q = 0; q < E; ++q) red[grp][lane * E + q] += red[grp + h][lane * E + q];
+    }
+    __syncthreads();
+  }
+  if (grp == 0) {
+#pragma unroll
+    for (int q = 0; q < E; ++q) acc[q] = red[0][lane * E + q];
+    if (FUSED) {
+      if (rp) fr.template update_store<LANES>(rp, lane, D, acc, o);
+    } else {
+      store_vals<float, E>(grad_unique + static_cast<int64_t>(u) * D + lane * E, acc);
+    }
+  }
+  __syncthreads();  // red is reused by the block's next key
+}
+
 template <typename WT, int E, int LANES, bool FUSED>
 __global__ __launch_bounds__(kBlock) void k_bwd_long_finish(TableDev t, Work w, float* __restrict__ grad_unique,
                                                             OptArgs o) {
-  constexpr int GPB = kBlock / LANES;
-  constexpr int D = LANES * E;
-  __shared__ float red[GPB][D];
-  const int lane = threadIdx.x % LANES;
-  const int grp = threadIdx.x / LANES;
+  __shared__ float red[kBlock / LANES][LANES * E];
   const int64_t nlong = w.scal[kCNLong];
-  for (int64_t li = blockIdx.x; li < nlong; li += gridDim.x) {
-    const int u = w.long_u[li];
-    const Seg sg = w.useg[u];
-    const int nu = unit_count(sg.count);
-    const int64_t u0 = w.long_start[li];
-    RowFrag<WT, E> fr;
-    uint8_t* rp = nullptr;
-    if (FUSED && grp == 0 && sg.row >= 0) {
-      rp = t.store.row(sg.row);
-      fr.load(rp, lane, D, t.nstate, t.rowscalar);  // in flight while the partial rows are read
-    }
+  for (int64_t li = blockIdx.x; li < nlong; li += gridDim.x)
+    finish_key<WT, E, LANES, FUSED, false>(t, w, li, grad_unique, o, red);
+}
+
+// A small batch (n <= kSmallIds): the launches themselves are its time, so one
+// launch takes both strategies: blocks [0, short_blocks) the short keys, each
+// other block one unit of a hot key.  The block that ends a key's last unit (a
+// counter per key, no waiting) finishes the key.  A unit per block, not per
+// lane group: the keys' finishes, each a chain of dependent loads, then run on
+// as many blocks (with the units of ten keys in one block they followed each
+// other: 34 us for the launch, 4750 ids).  The partial rows travel as
+// agent-scope accesses, complete (vmcnt 0) before their count: a device-scope
+// release fence would write back the L2.  4750 ids, dim 16: 8.0 us; the list,
+// short-key, unit and finish launches took 8.4 + 8.2 + 4.4 + 4.5 us.
+template <typename WT, typename GT, int LANES, int MODE, bool FUSED>
+__global__ __launch_bounds__(kBlock) void k_bwd_small(TableDev t, Work w, uint32_t nref, const GT* __restrict__ grad,
+                                                      float* __restrict__ grad_unique, OptArgs o, int short_blocks) {
+  constexpr int E = 16 / static_cast<int>(sizeof(GT));
+  constexpr int D = LANES * E;
+  __shared__ float red[kBlock / LANES][D];
+  __shared__ int done;
+  if (static_cast<int>(blockIdx.x) < short_blocks) {
+    bwd_short<WT, GT, LANES, MODE, FUSED>(t, w, nref, grad, grad_unique, o, blockIdx.x, short_blocks);
+    return;
+  }
+  const int64_t unit = static_cast<int64_t>(blockIdx.x) - short_blocks;
+  if (unit >= w.scal[kCNUnits]) return;  // the whole block
+  const Unit un = w.units[unit];
+  if (threadIdx.x < LANES) {
+    const int lane = threadIdx.x;
     float acc[E];
 #pragma unroll
     for (int q = 0; q < E; ++q) acc[q] = 0.f;
-    for (int j = grp; j < nu; j += 2 * GPB) {
-      float x[E], y[E];
-      load_vals<float, E>(w.gpart + (u0 + j) * D + lane * E, x);
-      const bool two = j + GPB < nu;
-      if (two) load_vals<float, E>(w.gpart + (u0 + j + GPB) * D + lane * E, y);
-#pragma unroll
-      for (int q = 0; q < E; ++q) acc[q] += x[q];
-      if (two) {
-#pragma unroll
-        for (int q = 0; q < E; ++q) acc[q] += y[q];
-      }
+    for (int p = un.p0; p < un.p1; p += kUnit)
+      sum_positions<GT, E, LANES, MODE>(w, grad, nref, p, min(kUnit, un.p1 - p), lane, acc);
+    store_agent<E>(w.gpart + unit * D + lane * E, acc);
+    const int nu = unit_count(w.useg[w.long_u[un.li]].count);
+    __builtin_amdgcn_s_waitcnt(0);  // the partial row (one wave's) is complete
+    if (lane == 0) {
+      const bool last = atomicAdd(&w.id_ref[un.li], 1) == nu - 1;
+      if (last) w.id_ref[un.li] = 0;  // ready for another backward of this context
+      done = last;
     }
-#pragma unroll
-    for (int q = 0; q < E; ++q) red[grp][lane * E + q] = acc[q];
-    __syncthreads();
-    for (int h = GPB / 2; h >= 1; h >>= 1) {
-      if (grp < h) {
-#pragma unroll
-        for (int q = 0; q < E; ++q) red[grp][lane * E + q] += red[grp + h][lane * E + q];
-      }
-      __syncthreads();
-    }
-    if (grp == 0) {
-#pragma unroll
-      for (int q = 0; q < E; ++q) acc[q] = red[0][lane * E + q];
-      if (FUSED) {
-        if (rp) fr.template update_store<LANES>(rp, lane, D, acc, o);
-      } else {
-        store_vals<float, E>(grad_unique + static_cast<int64_t>(u) * D + lane * E, acc);
-      }
-    }
-    __syncthreads();  // red is reused by the block's next key
   }
+  __syncthreads();
+  if (done) finish_key<WT, E, LANES, FUSED, true>(t, w, un.li, grad_unique, o, red);
 }
 
 // The occurrence list the backward reads: position occ_pos[i] of id i
@@ -529,6 +614,14 @@ static hipError_t bwd_launch(const TableDev& t, const Work& w, uint32_t nref, in
   // (short keys: their kernel; hot keys: unit sums start to finish end)
   hipEvent_t s0 = ev_s ? ev_s[0] : nullptr, s1 = ev_s ? ev_s[1] : nullptr;
   hipEvent_t l0 = ev_l ? ev_l[0] : nullptr, l1 = ev_l ? ev_l[1] : nullptr;
+  if (small_batch(n)) {  // one launch; the hot-key events have nothing of their own to bracket
+    const unsigned sb = grid_for(n, GPB, kResident), ub = static_cast<unsigned>(2 * (n / kUnit) + 2);
+    hipExtLaunchKernelGGL((k_bwd_small<WT, GT, LANES, MODE, FUSED>), dim3(sb + ub), dim3(kBlock), 0, s, s0, s1, 0, t, w,
+                          nref, g, gu, o, static_cast<int>(sb));
+    if (l0) (void)hipEventRecord(l0, s);
+    if (l1) (void)hipEventRecord(l1, s);
+    return hipGetLastError();
+  }
   hipExtLaunchKernelGGL((k_bwd_short<WT, GT, LANES, MODE, FUSED>), dim3(grid_for(n, GPB, kResident)), dim3(kBlock), 0,
                         s, s0, s1, 0, t, w, nref, g, gu, o);
   // one lane group per possible unit (the device-side count is at most
@@ -572,8 +665,13 @@ hipError_t launch_bwd(const TableDev& t, const Work& w, int64_t nref, int64_t n,
   if (n <= 0) return hipSuccess;
   {
     hipEvent_t e0 = ev_list ? ev_list[0] : nullptr, e1 = ev_list ? ev_list[1] : nullptr;
-    const dim3 grid(static_cast<unsigned>((n + kDedupTile - 1) / kDedupTile));
-    hipExtLaunchKernelGGL(k_occ_list, grid, dim3(kOccListNT), 0, s, e0, e1, 0, w, n);
+    if (small_batch(n)) {  // the pool has written the list
+      if (e0) (void)hipEventRecord(e0, s);
+      if (e1) (void)hipEventRecord(e1, s);
+    } else {
+      const dim3 grid(static_cast<unsigned>((n + kDedupTile - 1) / kDedupTile));
+      hipExtLaunchKernelGGL(k_occ_list, grid, dim3(kOccListNT), 0, s, e0, e1, 0, w, n);
+    }
   }
   const OptArgs o = opt ? *opt : OptArgs{0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f, 0.f, 0.f};
   if (opt)

@@ -25,6 +25,8 @@
 //   k_occ_init       per occurrence: unique id (inverse), row, position in the
 //                    occurrence list, hot-key backward units.  Its other
 //                    blocks write the initial rows of the new keys
+// A batch of at most kSmallIds ids on a table that need not grow takes two
+// launches instead of these six: k_small_dedup and k_small_rows.
 #include "device_common.h"
 
 #include <algorithm>
@@ -694,23 +696,40 @@ __device__ inline void publish_live(int64_t* h_live, int64_t tag, int64_t live) 
 // tombstones) and the Blocks (free rows, then provisioned ones) allow.  The
 // first min(inserted, F) new keys take free rows.  The published count
 // bounds both the IDMap occupancy and the rows allocated.
-__device__ inline void reserve_rows(int64_t* cscal, int64_t* tscal, int64_t req, int64_t hw, int64_t keys, int64_t F,
-                                    int64_t* h_live, int64_t tag) {
-  const int64_t tombs = tscal[kTTomb];
-  const int64_t key_room = max(tscal[kTLimit] - keys - tombs, int64_t(0));
-  const int64_t row_room = F + max(tscal[kTRowCap] - hw, int64_t(0));
+struct Reservation {
+  int64_t ins, hw, ftop, take;  // inserted, rows allocated and free rows before, free rows taken
+  int64_t published;            // the live count's bound after the call
+};
+
+// tcap: {key limit, provisioned rows, tombstones} of the table
+__device__ inline Reservation reservation(int64_t req, int64_t hw, int64_t keys, int64_t F, const int64_t (&tcap)[3]) {
+  const int64_t tombs = tcap[2];
+  const int64_t key_room = max(tcap[0] - keys - tombs, int64_t(0));
+  const int64_t row_room = F + max(tcap[1] - hw, int64_t(0));
   const int64_t ins = min(req, min(key_room, row_room));
   const int64_t take = min(ins, F);
-  cscal[kCNew] = ins;
-  cscal[kCBaseLive] = hw;
+  return Reservation{ins, hw, F, take, max(keys + ins + tombs, hw + ins - take)};
+}
+
+__device__ inline void store_reservation(int64_t* cscal, int64_t* tscal, int64_t req, int64_t keys,
+                                         const Reservation& r) {
+  cscal[kCNew] = r.ins;
+  cscal[kCBaseLive] = r.hw;
   cscal[kCBaseKeys] = keys;
-  cscal[kCFreeTop] = F;
-  cscal[kCFreeTake] = take;
-  cscal[kCTrunc] = req > ins ? 1 : 0;
-  tscal[kTLive] = hw + ins - take;
-  tscal[kTKeys] = keys + ins;
-  tscal[kTFree] = F - take;
-  publish_live(h_live, tag, max(keys + ins + tombs, hw + ins - take));
+  cscal[kCFreeTop] = r.ftop;
+  cscal[kCFreeTake] = r.take;
+  cscal[kCTrunc] = req > r.ins ? 1 : 0;
+  tscal[kTLive] = r.hw + r.ins - r.take;
+  tscal[kTKeys] = keys + r.ins;
+  tscal[kTFree] = r.ftop - r.take;
+}
+
+__device__ inline void reserve_and_publish(int64_t* cscal, int64_t* tscal, int64_t req, int64_t hw, int64_t keys,
+                                           int64_t F, int64_t* h_live, int64_t tag) {
+  const int64_t tcap[3] = {tscal[kTLimit], tscal[kTRowCap], tscal[kTTomb]};
+  const Reservation r = reservation(req, hw, keys, F, tcap);
+  store_reservation(cscal, tscal, req, keys, r);
+  publish_live(h_live, tag, r.published);
 }
 
 // Scan of the five tile-sum arrays: block c scans chunk c (kScanChunk tiles,
@@ -796,12 +815,13 @@ __global__ __launch_bounds__(1024) void k_scan5(int32_t* __restrict__ bsum, int6
   cscal[kCNewReq] = tot[2];
   cscal[kCNLong] = tot[3];
   cscal[kCNUnits] = tot[4];
-  reserve_rows(cscal, tscal, tot[2], tscal[kTLive], tscal[kTKeys], tscal[kTFree], h_live, tag);
+  reserve_and_publish(cscal, tscal, tot[2], tscal[kTLive], tscal[kTKeys], tscal[kTFree], h_live, tag);
 }
 
 // After the host grew the table: reserve again from the same counts.
 __global__ void k_rereserve(int64_t* cscal, int64_t* tscal, int64_t* h_live, int64_t tag) {
-  reserve_rows(cscal, tscal, cscal[kCNewReq], cscal[kCBaseLive], cscal[kCBaseKeys], cscal[kCFreeTop], h_live, tag);
+  reserve_and_publish(cscal, tscal, cscal[kCNewReq], cscal[kCBaseLive], cscal[kCBaseKeys], cscal[kCFreeTop], h_live,
+                      tag);
 }
 
 __global__ void k_zero_scalars(int64_t* cscal) { cscal[threadIdx.x] = 0; }
@@ -957,56 +977,59 @@ __device__ inline float init_value(uint64_t z, int j, float lo, float span) {
   return __builtin_fmaf(u, span, lo);
 }
 
-// Lane groups of 16 write the rows of the inserted keys: w from the init
+// A lane group of 16 (lane = 0 ... 15) writes a new key's row: w from the init
 // formula, optimizer state zero, and for eviction the key and this call's
-// clock; 16 bytes per lane per store.  Block `blk` of `nblk` takes every
-// nblk-th group of keys.
-__device__ inline void init_rows(const TableDev& t, const Work& w, int64_t blk, int64_t nblk) {
-  constexpr int G = 16;
-  const int lane = threadIdx.x % G, grp = threadIdx.x / G;
-  const int64_t inserted = w.scal[kCNew];
+// clock; 16 bytes per lane per store.
+constexpr int kInitLanes = 16;
+
+__device__ inline void init_row(const TableDev& t, int64_t row, int64_t key, int lane) {
   const int chunks = static_cast<int>(t.store.stride / 16);
   const int wbytes = t.dim * (t.row_dtype ? 2 : 4);
-  for (int64_t q = blk * (kBlock / G) + grp; q < inserted; q += nblk * (kBlock / G)) {
-    const int u = w.new_list[q];
-    if (u < 0) continue;
-    const int64_t row = w.useg[u].row;
-    const int64_t key = w.unique[u];
-    const uint64_t z = mix64(static_cast<uint64_t>(key) ^ mix64(t.seed));
-    uint8_t* rp = t.store.row(row);
-    for (int ch = lane; ch < chunks; ch += G) {
-      const int off = ch * 16;
-      uint4 val = make_uint4(0u, 0u, 0u, 0u);
-      if (off < wbytes) {
-        if (t.row_dtype == 0) {
-          const int j0 = off / 4;
-          val = make_uint4(__float_as_uint(init_value(z, j0, t.lo, t.span)),
-                           __float_as_uint(init_value(z, j0 + 1, t.lo, t.span)),
-                           __float_as_uint(init_value(z, j0 + 2, t.lo, t.span)),
-                           __float_as_uint(init_value(z, j0 + 3, t.lo, t.span)));
-        } else {
-          const int j0 = off / 2;
-          uint32_t h[4];
+  const uint64_t z = mix64(static_cast<uint64_t>(key) ^ mix64(t.seed));
+  uint8_t* rp = t.store.row(row);
+  for (int ch = lane; ch < chunks; ch += kInitLanes) {
+    const int off = ch * 16;
+    uint4 val = make_uint4(0u, 0u, 0u, 0u);
+    if (off < wbytes) {
+      if (t.row_dtype == 0) {
+        const int j0 = off / 4;
+        val = make_uint4(__float_as_uint(init_value(z, j0, t.lo, t.span)),
+                         __float_as_uint(init_value(z, j0 + 1, t.lo, t.span)),
+                         __float_as_uint(init_value(z, j0 + 2, t.lo, t.span)),
+                         __float_as_uint(init_value(z, j0 + 3, t.lo, t.span)));
+      } else {
+        const int j0 = off / 2;
+        uint32_t h[4];
 #pragma unroll
-          for (int k = 0; k < 4; ++k)
-            h[k] = static_cast<uint32_t>(f32_to_bf16(init_value(z, j0 + 2 * k, t.lo, t.span))) |
-                   (static_cast<uint32_t>(f32_to_bf16(init_value(z, j0 + 2 * k + 1, t.lo, t.span))) << 16);
-          val = make_uint4(h[0], h[1], h[2], h[3]);
-        }
+        for (int k = 0; k < 4; ++k)
+          h[k] = static_cast<uint32_t>(f32_to_bf16(init_value(z, j0 + 2 * k, t.lo, t.span))) |
+                 (static_cast<uint32_t>(f32_to_bf16(init_value(z, j0 + 2 * k + 1, t.lo, t.span))) << 16);
+        val = make_uint4(h[0], h[1], h[2], h[3]);
       }
-      if (t.meta_off >= 0 && off + 16 > t.meta_off && off < t.meta_off + 12) {
-        uint32_t v4[4] = {val.x, val.y, val.z, val.w};
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int b = off + 4 * q4 - t.meta_off;  // byte of the {key, clock} record
-          if (b == 0) v4[q4] = static_cast<uint32_t>(static_cast<uint64_t>(key));
-          if (b == 4) v4[q4] = static_cast<uint32_t>(static_cast<uint64_t>(key) >> 32);
-          if (b == 8) v4[q4] = t.clock;
-        }
-        val = make_uint4(v4[0], v4[1], v4[2], v4[3]);
-      }
-      *reinterpret_cast<uint4*>(rp + off) = val;
     }
+    if (t.meta_off >= 0 && off + 16 > t.meta_off && off < t.meta_off + 12) {
+      uint32_t v4[4] = {val.x, val.y, val.z, val.w};
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int b = off + 4 * q4 - t.meta_off;  // byte of the {key, clock} record
+        if (b == 0) v4[q4] = static_cast<uint32_t>(static_cast<uint64_t>(key));
+        if (b == 4) v4[q4] = static_cast<uint32_t>(static_cast<uint64_t>(key) >> 32);
+        if (b == 8) v4[q4] = t.clock;
+      }
+      val = make_uint4(v4[0], v4[1], v4[2], v4[3]);
+    }
+    *reinterpret_cast<uint4*>(rp + off) = val;
+  }
+}
+
+// The rows of the inserted keys: block `blk` of `nblk` takes every nblk-th
+// group of keys.
+__device__ inline void init_rows(const TableDev& t, const Work& w, int64_t blk, int64_t nblk) {
+  constexpr int G = kInitLanes;
+  const int64_t inserted = w.scal[kCNew];
+  for (int64_t q = blk * (kBlock / G) + threadIdx.x / G; q < inserted; q += nblk * (kBlock / G)) {
+    const int u = w.new_list[q];
+    if (u >= 0) init_row(t, w.useg[u].row, w.unique[u], threadIdx.x % G);
   }
 }
 
@@ -1099,6 +1122,322 @@ hipError_t launch_compact_insert(const int64_t* values, int64_t n, const TableDe
   else k_occ_init<false><<<static_cast<unsigned>(ob + ib), kBlock, 0, s>>>(t, w, n, ob);
   if (ev_occ && ev_occ[1]) (void)hipEventRecord(ev_occ[1], s);
   if (ev_init && ev_init[1]) (void)hipEventRecord(ev_init[1], s);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// a small batch: the front end in two launches
+// ---------------------------------------------------------------------------
+//
+// At most kSmallIds ids: every launch of the general front end is a chain of
+// dependent memory trips of 4-12 us here (46 us for 4750 ids; two partitions
+// of 3300 distinct ids each even fall into the sweeps: 123 us for 6656 ids).
+//   k_small_dedup  block b takes the ids of hash partition b: LDS dedup and
+//                  the IDMap probe of each key, results by position
+//   k_small_rows   every block scans the counts of all positions (unique ids,
+//                  segments, new keys); the ids are split over the blocks,
+//                  which insert, write the new rows and every result
+// Several blocks because one CU has too few misses in flight for the probes
+// (7 us for 4096 keys) and issues the per-id work too slowly: the same front
+// end in one block plus a launch for the new rows took 23 us for 4750 ids and
+// 31 us for 6656, these two 14.7 and 15.5 us.
+// Any split of the keys over the blocks fits: the LDS arrays hold the whole
+// batch.
+
+constexpr int kSmallNT = 1024;
+constexpr int kSmallPT = kSmallIds / kSmallNT;  // positions per thread
+constexpr int kSmallPart = 512;                  // ids per block, about
+constexpr uint32_t kSmallNew = 0x80000000u;      // in a count: the key was not found
+
+// The partition of an encoded key (2^logG partitions).
+__device__ inline uint32_t small_part(unsigned long long e, int logG) {
+  const uint32_t x = (static_cast<uint32_t>(e) ^ static_cast<uint32_t>(e >> 32) * 0x9E3779B1u) * 0x85EBCA6Bu;
+  return logG == 0 ? 0u : (x ^ (x >> 15)) * 0xC2B2AE35u >> (32 - logG);
+}
+
+// What the two launches hand over beside the results' own arrays, in arrays of
+// the general passes: the counts by position, the table's scalars as they were
+// before the call (the second launch changes them).
+__device__ inline uint32_t* small_counts(const Work& w) { return reinterpret_cast<uint32_t*>(w.ptmp); }
+__device__ inline int64_t* small_scalars(const Work& w) { return reinterpret_cast<int64_t*>(w.bsum); }
+static_assert(kTScalars * sizeof(int64_t) <= 5 * (kDedupTile / kRankTile) * sizeof(int32_t),
+              "the smallest tile-sum array holds the table's scalars");
+
+// Per id i of the block's partition: occ_word = first position of its key << 16
+// | rank among the key's ids (kOccRejected for a reserved key), and its count:
+// at a first position the key's count | kSmallNew if it was not found (and
+// occ_row = its row), 0 elsewhere.
+__global__ __launch_bounds__(kSmallNT) void k_small_dedup(const int64_t* __restrict__ values, int n, int logG, TableDev t,
+                                                          Work w) {
+  constexpr int NT = kSmallNT, PT = kSmallPT;
+  constexpr unsigned int kNone = 0xFFFFFFFFu;
+  constexpr int kIdx = 13;  // bits of a member index
+  static_assert(kSmallIds <= 1 << kIdx, "slot = first position << kIdx | member, below kNone");
+  __shared__ unsigned long long lkey[kSmallIds];           // the members' keys
+  __shared__ alignas(16) unsigned int slot[kSmallIds];     // LDS hash: smallest (position, member) of the slot's key
+  __shared__ alignas(16) unsigned int cnt2[kSmallIds / 2]; // occurrences by first member, 16 bits each
+  __shared__ unsigned short lpos[kSmallIds], lslot[kSmallIds];
+  __shared__ int members;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  unsigned long long e[PT];
+#pragma unroll
+  for (int k = 0; k < PT; ++k)  // clamped, not skipped: all in flight together
+    e[k] = static_cast<unsigned long long>(values[min(k * NT + tid, n - 1)]) ^ kSign;
+  if (tid == 0) members = 0;
+  for (int q = tid; q < kSmallIds / 4; q += NT) reinterpret_cast<uint4*>(slot)[q] = make_uint4(kNone, kNone, kNone, kNone);
+  for (int q = tid; q < kSmallIds / 8; q += NT) reinterpret_cast<uint4*>(cnt2)[q] = make_uint4(0u, 0u, 0u, 0u);
+  if (blockIdx.x == 0 && tid < kTScalars) small_scalars(w)[tid] = t.scal[tid];
+  __syncthreads();
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int k = 0; k < PT; ++k) {
+    if (k * NT >= n) continue;  // block-uniform
+    const int i = k * NT + tid;
+    bool mine = i < n && small_part(e[k], logG) == blockIdx.x;
+    if (mine && e[k] <= kEncTomb) {
+      atomicOr(reinterpret_cast<int*>(&t.scal[kTErr]), kErrKey);
+      w.occ_word[i] = kOccRejected;
+      small_counts(w)[i] = 0u;
+      mine = false;
+    }
+    const uint64_t b = __ballot(mine);
+    int at = 0;
+    if (lane == 0 && b) at = atomicAdd(&members, __popcll(b));
+    at = __shfl(at, 0, kWave) + __popcll(b & below);
+    if (mine) {
+      lkey[at] = e[k];
+      lpos[at] = static_cast<unsigned short>(i);
+    }
+  }
+  __syncthreads();
+  const int M = members;
+  for (int m = tid; m < M; m += NT) {
+    const unsigned long long key = lkey[m];
+    const unsigned int x = static_cast<unsigned int>(lpos[m]) << kIdx | static_cast<unsigned int>(m);
+    unsigned int sl = static_cast<unsigned int>(idmap_hash(key) >> 40) & (kSmallIds - 1);
+    while (true) {  // at most as many keys as slots: terminates
+      const unsigned int old = atomicCAS(&slot[sl], kNone, x);
+      if (old == kNone) break;
+      if (lkey[old & (kSmallIds - 1)] == key) {  // a slot only ever changes to a smaller position of its key
+        if (x < old) atomicMin(&slot[sl], x);
+        break;
+      }
+      sl = (sl + 1) & (kSmallIds - 1);
+    }
+    lslot[m] = static_cast<unsigned short>(sl);
+  }
+  __syncthreads();
+  for (int m = tid; m < M; m += NT) {
+    const unsigned int f = slot[lslot[m]];
+    const int fm = static_cast<int>(f & (kSmallIds - 1)), sft = (fm & 1) * 16;
+    const unsigned int rank = (atomicAdd(&cnt2[fm >> 1], 1u << sft) >> sft) & 0xFFFFu;
+    w.occ_word[lpos[m]] = (f >> kIdx) << 16 | rank;
+  }
+  __syncthreads();
+  for (int m = tid; m < M; m += NT) {
+    const int i = lpos[m];
+    uint32_t c = 0u;
+    if (static_cast<int>(slot[lslot[m]] & (kSmallIds - 1)) == m) {
+      const int64_t r = idmap_lookup(t, lkey[m]);
+      c = (cnt2[m >> 1] >> ((m & 1) * 16)) & 0xFFFFu;
+      if (r < 0) c |= kSmallNew;
+      w.occ_row[i] = r;
+    }
+    small_counts(w)[i] = c;
+  }
+}
+
+template <bool OCC>
+__global__ __launch_bounds__(kSmallNT) void k_small_rows(const int64_t* __restrict__ values, int n, TableDev t, Work w,
+                                                         int64_t* h_live, int64_t tag, int64_t* __restrict__ rows_out,
+                                                         int64_t* n_inserted) {
+  constexpr int NT = kSmallNT, PT = kSmallPT, NW = NT / kWave;
+  static_assert(PT == 8 && kSmallIds < 1 << 15, "sums of a call fit 16 bits; 8 positions in two 16-byte loads");
+  __shared__ unsigned int info[kSmallIds];        // by first position: unique id << 16 | start of its segment
+  __shared__ unsigned short lnew[kSmallIds];      // by first position: 1 + rank among the keys not found, or 0
+  // hot keys: unique id, segment start, occurrences, first unit
+  __shared__ unsigned short hotu[kSmallIds / kLong], hotst[kSmallIds / kLong], hotc[kSmallIds / kLong],
+      hotunit[kSmallIds / kLong];
+  __shared__ int sh[NW][3];
+  __shared__ int64_t newrow[kSmallPart], newkey[kSmallPart];
+  __shared__ int nnew;
+  int* const err = reinterpret_cast<int*>(&t.scal[kTErr]);
+  const int64_t* const tsc = small_scalars(w);
+  const uint32_t* const counts = small_counts(w);
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+  // positions 8 tid ... 8 tid + 7: the first occurrences among them
+  uint32_t cw[PT];
+  {
+    const int p0 = tid * PT;
+    if (p0 + PT <= n) {
+      const uint4 a = *reinterpret_cast<const uint4*>(counts + p0);
+      const uint4 b = *reinterpret_cast<const uint4*>(counts + p0 + 4);
+      cw[0] = a.x; cw[1] = a.y; cw[2] = a.z; cw[3] = a.w;
+      cw[4] = b.x; cw[5] = b.y; cw[6] = b.z; cw[7] = b.w;
+    } else {
+#pragma unroll
+      for (int k = 0; k < PT; ++k) cw[k] = p0 + k < n ? counts[p0 + k] : 0u;
+    }
+  }
+  // this block's ids, one per thread (kSmallPart of them)
+  const int i = blockIdx.x * kSmallPart + tid;
+  const bool act = tid < kSmallPart && i < n;
+  const uint32_t ow = act ? w.occ_word[i] : kOccRejected;
+  const int f = ow == kOccRejected ? -1 : static_cast<int>(ow >> 16);
+  const int64_t found = f >= 0 ? w.occ_row[f] : -1;  // another block may store the same row there (not for a new key)
+  const int own = act ? static_cast<int>(counts[i] & 0xFFFFu) : 0;
+  const unsigned long long e = act ? static_cast<unsigned long long>(values[i]) ^ kSign : kEncEmpty;
+  const int64_t hw = tsc[kTLive], keys = tsc[kTKeys], F = tsc[kTFree];
+  const int64_t tcap[3] = {tsc[kTLimit], tsc[kTRowCap], tsc[kTTomb]};
+  if (tid == 0) nnew = 0;
+  // occurrences | keys << 16; units | hot keys << 16; keys not found
+  int v[3] = {0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < PT; ++k) {
+    const int c = static_cast<int>(cw[k] & 0xFFFFu);
+    v[0] += c + (c > 0 ? 1 << 16 : 0);
+    if (c > kLong) v[1] += unit_count(c) + (1 << 16);
+    v[2] += cw[k] >> 31;
+  }
+  int inc[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) inc[a] = wave_incl_scan(v[a]);
+  if (lane == kWave - 1) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) sh[wid][a] = inc[a];
+  }
+  __syncthreads();
+  int ex[3], tot[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {  // every wave sums the waves before it
+    int before = 0, all = 0;
+    for (int q = 0; q < NW; ++q) {
+      before += q < wid ? sh[q][a] : 0;
+      all += sh[q][a];
+    }
+    ex[a] = before + inc[a] - v[a];
+    tot[a] = all;
+  }
+#pragma unroll
+  for (int k = 0; k < PT; ++k) {
+    const int c = static_cast<int>(cw[k] & 0xFFFFu);
+    if (c == 0) continue;
+    const int p = tid * PT + k;
+    info[p] = static_cast<unsigned int>(ex[0]);
+    ex[0] += c + (1 << 16);
+    lnew[p] = cw[k] >> 31 ? static_cast<unsigned short>(ex[2] + 1) : 0;
+    ex[2] += cw[k] >> 31;
+    if (c > kLong) {
+      const int q = ex[1] >> 16;
+      hotu[q] = static_cast<unsigned short>(info[p] >> 16);
+      hotst[q] = static_cast<unsigned short>(info[p] & 0xFFFFu);
+      hotc[q] = static_cast<unsigned short>(c);
+      hotunit[q] = static_cast<unsigned short>(ex[1] & 0xFFFF);
+      ex[1] += unit_count(c) + (1 << 16);
+    }
+  }
+  const int nhot = tot[1] >> 16, nunits = tot[1] & 0xFFFF;
+  const Reservation res = reservation(tot[2], hw, keys, F, tcap);
+  if (blockIdx.x == 0 && tid == 0) {
+    store_reservation(w.scal, t.scal, tot[2], keys, res);
+    w.scal[kCU] = tot[0] >> 16;
+    w.scal[kCValid] = tot[0] & 0xFFFF;
+    w.scal[kCNewReq] = tot[2];
+    w.scal[kCNLong] = nhot;
+    w.scal[kCNUnits] = nunits;
+    if (tot[2] > res.ins) atomicOr(err, kErrFull);
+    if (n_inserted) *n_inserted = res.ins;
+  }
+  __syncthreads();
+  int64_t r = found;
+  unsigned int x = 0u;
+  if (f >= 0) {
+    x = info[f];
+    const int64_t q = static_cast<int64_t>(lnew[f]) - 1;
+    // the first `take` new keys take free rows from the top of the stack
+    if (q >= 0) r = q >= res.ins ? -1 : q < res.take ? t.free_rows[res.ftop - 1 - q] : res.hw + (q - res.take);
+    if (f == i) {  // the key's first occurrence
+      const int u = static_cast<int>(x >> 16);
+      if (q >= 0 && r >= 0) {
+        const int64_t sl = idmap_claim(t, e);
+        if (sl >= 0) {
+          t.slots[sl].row = r;
+          const int z = atomicAdd(&nnew, 1);
+          newrow[z] = r;
+          newkey[z] = static_cast<int64_t>(e ^ kSign);
+        } else {
+          atomicOr(err, kErrProbe);  // no slot: cannot happen below the key limit
+        }
+      } else if (r >= 0 && t.meta_off >= 0) {
+        // eviction: this call is the key's last lookup
+        *reinterpret_cast<uint32_t*>(t.store.row(r) + t.meta_off + 8) = t.clock;
+      }
+      w.unique[u] = static_cast<int64_t>(e ^ kSign);
+      w.rows[u] = r;
+      w.useg[u] = Seg{r, static_cast<int>(x & 0xFFFFu), own};
+    }
+  }
+  __syncthreads();
+  // the rows of the block's new keys
+  for (int z = tid / kInitLanes; z < nnew; z += NT / kInitLanes) init_row(t, newrow[z], newkey[z], tid % kInitLanes);
+  if (act) {
+    if (OCC) {
+      w.inverse[i] = f >= 0 ? static_cast<int>(x >> 16) : -1;
+      w.occ_row[i] = r;
+      w.occ_ref[i] = -1;  // no gradient row yet: the pool writes them
+      w.occ_pos[i] = f >= 0 ? static_cast<int>(x & 0xFFFFu) + static_cast<int>(ow & 0xFFFFu) : -1;
+    } else {
+      rows_out[i] = r;
+    }
+  }
+  if (OCC && blockIdx.x == 0) {
+    for (int q = tid; q < nhot; q += NT) {
+      w.long_u[q] = hotu[q];
+      w.long_start[q] = hotunit[q];
+      w.id_ref[q] = 0;  // (no small batch's gradient rows) the backward's count of the key's finished units
+    }
+    for (int y = tid; y < nunits; y += NT) {
+      int lo = 0, hi = nhot;  // the hot key of unit y: hotunit[lo] <= y < hotunit[lo + 1]
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (hotunit[mid] <= y) lo = mid;
+        else hi = mid;
+      }
+      const int c = hotc[lo], usz = kUnit << unit_shift(c), j = y - hotunit[lo];
+      w.units[y] = Unit{lo, hotst[lo] + j * usz, hotst[lo] + min((j + 1) * usz, c), 0};
+    }
+  }
+  if (blockIdx.x == 0 && tid == 0) publish_live(h_live, tag, res.published);  // last: a store to host memory
+}
+
+__global__ __launch_bounds__(kBlock) void k_clear_refs(Work w, int n) {
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  w.occ_ref[i] = -1;
+  w.id_ref[i] = 0;
+}
+
+hipError_t launch_clear_refs(const Work& w, int64_t n, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  k_clear_refs<<<grid_for(n, kBlock), kBlock, 0, s>>>(w, static_cast<int>(n));
+  return hipGetLastError();
+}
+
+hipError_t launch_small_front(const int64_t* values, int64_t n, const TableDev& t, const Work& w, bool occ_lists,
+                              int64_t* h_live, int64_t tag, int64_t* rows_out, int64_t* n_inserted,
+                              hipEvent_t* ev_front, hipEvent_t* ev_rows, hipStream_t s) {
+  if (n <= 0 || n > kSmallIds) return hipErrorInvalidValue;
+  const int ni = static_cast<int>(n);
+  int logG = 0;
+  while (kSmallPart << logG < ni) ++logG;
+  if (ev_front && ev_front[0]) (void)hipEventRecord(ev_front[0], s);
+  k_small_dedup<<<1u << logG, kSmallNT, 0, s>>>(values, ni, logG, t, w);
+  if (ev_front && ev_front[1]) (void)hipEventRecord(ev_front[1], s);
+  if (ev_rows && ev_rows[0]) (void)hipEventRecord(ev_rows[0], s);
+  const unsigned nb = grid_for(n, kSmallPart);
+  if (occ_lists) k_small_rows<true><<<nb, kSmallNT, 0, s>>>(values, ni, t, w, h_live, tag, nullptr, nullptr);
+  else k_small_rows<false><<<nb, kSmallNT, 0, s>>>(values, ni, t, w, h_live, tag, rows_out, n_inserted);
+  if (ev_rows && ev_rows[1]) (void)hipEventRecord(ev_rows[1], s);
   return hipGetLastError();
 }
 

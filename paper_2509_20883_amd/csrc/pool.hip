@@ -7,7 +7,8 @@
 // occurrence its row (occ_row); these kernels read each occurrence's row
 // with 16-byte vector loads, one lane group of D*sizeof(row)/16 lanes per
 // row, and write the gradient row of each id (id_ref, in id order), from
-// which the backward builds its occurrence list.
+// which the backward builds its occurrence list (a small batch's list is
+// written here).
 //
 // A lane group handles one bag per lane and requests 16 rows of them at a
 // time, for single-id and long bags alike.
@@ -26,6 +27,15 @@ __device__ inline void record_pooled_range(const Work& w, const int64_t* offsets
   const int64_t lo = min(max(offsets[0], int64_t(0)), n);
   w.scal[kCIdLo] = lo;
   w.scal[kCIdHi] = min(max(offsets[bags], lo), n);
+}
+
+// Gradient row of id i: kept in id order for the backward's list launch, or,
+// for a small batch, put at the id's place in the occurrence list at once
+// (pos: occ_pos[i], -1 for an id that takes no part).
+template <bool SMALL>
+__device__ inline void write_ref(const Work& w, int64_t i, int pos, int ref) {
+  if (!SMALL) w.id_ref[i] = ref;
+  else if (pos >= 0) w.occ_ref[pos] = ref;
 }
 
 // acc += the E row elements held raw in v (16 bytes of the row)
@@ -59,8 +69,8 @@ __device__ inline int64_t group_incl_scan(int64_t v, int lane) {
   return v;
 }
 
-// A lane group of LANES lanes pools LANES consecutive bags (lane q owns bag
-// g0 + q).  Their positions, taken as one sequence, are read in chunks of C:
+// A lane group of LANES lanes pools `per` <= LANES consecutive bags (lane q
+// owns bag g0 + q).  Their positions, taken as one sequence, are read in chunks of C:
 // the lanes load the chunk's occurrence rows and list positions (J per
 // lane), the next chunk's are requested before this chunk's rows are used,
 // and all C rows of a chunk are requested before any is added -- C rows in
@@ -72,9 +82,16 @@ __device__ inline int64_t group_incl_scan(int64_t v, int lane) {
 // For well-formed offsets (each bag starts where the previous one ends) the
 // sequence is positions offsets[g0] ... ; malformed offsets give wrong
 // sums, never an access outside [0, n).
-template <typename WT, int LANES, int MODE, int C>
+// Bags per lane group (a power of two): LANES, fewer where that would leave
+// the chip idle (under kPoolBlocks blocks, 4 per CU): a lane group's chunks
+// are a serial chain, so a small batch is split further (1024 bags of 4.6 ids,
+// dim 16: 4 blocks of 4 bags per group 9.9 us, 16 blocks of one bag 4.7 us,
+// the list written on the way).
+constexpr int64_t kPoolBlocks = 1024;
+
+template <typename WT, int LANES, int MODE, int C, bool SMALL>
 __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64_t* __restrict__ offsets, int64_t n,
-                                                 int64_t bags, float* __restrict__ out) {
+                                                 int64_t bags, int per, float* __restrict__ out) {
   constexpr int E = 16 / static_cast<int>(sizeof(WT));
   constexpr int D = LANES * E;
   constexpr int GPB = kBlock / LANES;
@@ -82,9 +99,9 @@ __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64
   const int lane = threadIdx.x % LANES;
   const int grp = threadIdx.x / LANES;
   if (blockIdx.x == 0 && threadIdx.x == 0) record_pooled_range(w, offsets, n, bags);
-  const int64_t g0 = (static_cast<int64_t>(blockIdx.x) * GPB + grp) * LANES;
+  const int64_t g0 = (static_cast<int64_t>(blockIdx.x) * GPB + grp) * per;
   if (g0 >= bags) return;
-  const int nb = static_cast<int>(min(static_cast<int64_t>(LANES), bags - g0));
+  const int nb = static_cast<int>(min(static_cast<int64_t>(per), bags - g0));
   // this lane's bag, CSR bounds clamped to [0, n]; positions fit 32 bits (n <= 2^28)
   const int n32 = static_cast<int>(n);
   const int64_t gq = g0 + min(lane, nb - 1);
@@ -142,6 +159,11 @@ __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64
       if (r >= 0) x[c] = *reinterpret_cast<const uint4*>(t.store.row(r) + lane * 16);
     }
     if (t0 + C < total) load_idx(t0 + C);  // the next chunk's row ids replace rr
+    int lp[J];  // small batch: list positions of this lane's ids of the chunk
+    if (SMALL) {
+#pragma unroll
+      for (int j = 0; j < J; ++j) lp[j] = w.occ_pos[min(p0 + t0 + min(lane + j * LANES, C - 1), n32 - 1)];
+    }
     int myq[J];  // bag of this lane's positions in the chunk
 #pragma unroll
     for (int c = 0; c < C; ++c) {
@@ -158,7 +180,7 @@ __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64
     for (int j = 0; j < J; ++j) {
       const int c = lane + j * LANES;
       if (c >= C || t0 + c >= total || p0 + t0 + c >= n32) continue;
-      w.id_ref[p0 + t0 + c] = static_cast<int>(g0 + myq[j]);
+      write_ref<SMALL>(w, p0 + t0 + c, SMALL ? lp[j] : 0, static_cast<int>(g0 + myq[j]));
     }
   }
   while (q < nb) flush();  // the last bag and any empty bags after it
@@ -166,7 +188,7 @@ __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64
 
 // Padded copy: block = (bag, TCH positions); a lane group copies TCH / groups
 // positions, with their loads issued together.
-template <typename WT, int LANES>
+template <typename WT, int LANES, bool SMALL>
 __global__ __launch_bounds__(kBlock) void k_pool_none(TableDev t, Work w, const int64_t* __restrict__ offsets,
                                                       int64_t n, int64_t bags, int64_t L, bool tail,
                                                       WT* __restrict__ out, uint8_t* __restrict__ mask) {
@@ -203,21 +225,24 @@ __global__ __launch_bounds__(kBlock) void k_pool_none(TableDev t, Work w, const 
       *reinterpret_cast<uint4*>(out + (g * L + tp[k]) * D + lane * E) = v[k];
       if (lane == 0) {
         mask[g * L + tp[k]] = tp[k] < len ? 1 : 0;
-        if (tp[k] < len) w.id_ref[b + skip + tp[k]] = static_cast<int>(g * L + tp[k]);
+        if (tp[k] < len)
+          write_ref<SMALL>(w, b + skip + tp[k], SMALL ? w.occ_pos[b + skip + tp[k]] : 0,
+                           static_cast<int>(g * L + tp[k]));
       }
     }
     if (c == 0 && lane == 0) {
       // ids outside the window (past L, or before skip): in the occurrence
       // list (the key is touched) but without a gradient row
       const int64_t x0 = tail ? 0 : L, x1 = tail ? skip : len;
-      for (int64_t tpos = x0 + grp; tpos < x1; tpos += GPB) w.id_ref[b + tpos] = -1;
+      for (int64_t tpos = x0 + grp; tpos < x1; tpos += GPB)
+        write_ref<SMALL>(w, b + tpos, SMALL ? w.occ_pos[b + tpos] : 0, -1);
     }
   }
 }
 
 // The launch takes optional start / stop events that the dispatch itself
 // timestamps (the kernel's own execution, no extra packets on the stream).
-template <typename WT, int LANES>
+template <typename WT, int LANES, bool SMALL>
 static hipError_t pool_mode(const TableDev& t, const Work& w, const int64_t* offsets, int64_t n, int64_t bags,
                             int mode, int64_t pad_len, void* out, uint8_t* mask, hipEvent_t e0, hipEvent_t e1,
                             hipStream_t s) {
@@ -225,34 +250,36 @@ static hipError_t pool_mode(const TableDev& t, const Work& w, const int64_t* off
   if (mode == 2 || mode == 3) {
     constexpr int TCH = GPB > 64 ? GPB : 64;
     const int64_t nch = (pad_len + TCH - 1) / TCH;
-    hipExtLaunchKernelGGL((k_pool_none<WT, LANES>), dim3(grid_for(bags * nch, 1, 1 << 20)), dim3(kBlock), 0, s, e0, e1,
-                          0, t, w, offsets, n, bags, pad_len, mode == 3, static_cast<WT*>(out), mask);
+    hipExtLaunchKernelGGL((k_pool_none<WT, LANES, SMALL>), dim3(grid_for(bags * nch, 1, 1 << 20)), dim3(kBlock), 0, s,
+                          e0, e1, 0, t, w, offsets, n, bags, pad_len, mode == 3, static_cast<WT*>(out), mask);
   } else {
-    // one lane group per LANES bags (one bag per lane), 16 rows in flight
+    // one lane group per `per` bags (one bag per lane), 16 rows in flight
     float* o = static_cast<float*>(out);
-    const unsigned g = grid_for(bags, static_cast<int64_t>(GPB) * LANES, int64_t(1) << 31);
+    int per = LANES;
+    while (per > 1 && (bags + per * GPB - 1) / (per * GPB) < kPoolBlocks) per >>= 1;
+    const unsigned g = grid_for(bags, static_cast<int64_t>(GPB) * per, int64_t(1) << 31);
     if (mode == 1)
-      hipExtLaunchKernelGGL((k_pool<WT, LANES, 1, 16>), dim3(g), dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n, bags,
-                            o);
+      hipExtLaunchKernelGGL((k_pool<WT, LANES, 1, 16, SMALL>), dim3(g), dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n,
+                            bags, per, o);
     else
-      hipExtLaunchKernelGGL((k_pool<WT, LANES, 0, 16>), dim3(g), dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n, bags,
-                            o);
+      hipExtLaunchKernelGGL((k_pool<WT, LANES, 0, 16, SMALL>), dim3(g), dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n,
+                            bags, per, o);
   }
   return hipGetLastError();
 }
 
-template <typename WT>
+template <typename WT, bool SMALL>
 static hipError_t pool_dim(const TableDev& t, const Work& w, const int64_t* offsets, int64_t n, int64_t bags, int mode,
                            int64_t pad_len, void* out, uint8_t* mask, hipEvent_t e0, hipEvent_t e1, hipStream_t s) {
   constexpr int E = 16 / static_cast<int>(sizeof(WT));
   switch (t.dim / E) {
-    case 1: return pool_mode<WT, 1>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 2: return pool_mode<WT, 2>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 4: return pool_mode<WT, 4>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 8: return pool_mode<WT, 8>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 16: return pool_mode<WT, 16>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 32: return pool_mode<WT, 32>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 64: return pool_mode<WT, 64>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 1: return pool_mode<WT, 1, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 2: return pool_mode<WT, 2, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 4: return pool_mode<WT, 4, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 8: return pool_mode<WT, 8, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 16: return pool_mode<WT, 16, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 32: return pool_mode<WT, 32, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 64: return pool_mode<WT, 64, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -261,9 +288,11 @@ hipError_t launch_pool(const TableDev& t, const Work& w, const int64_t* offsets,
                        int64_t pad_len, void* out, uint8_t* mask, hipEvent_t* ev, hipStream_t s) {
   if (bags <= 0) return hipSuccess;
   hipEvent_t e0 = ev ? ev[0] : nullptr, e1 = ev ? ev[1] : nullptr;
-  const hipError_t e = t.row_dtype ? pool_dim<uint16_t>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s)
-                                   : pool_dim<float>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-  return e;
+  if (small_batch(n))
+    return t.row_dtype ? pool_dim<uint16_t, true>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s)
+                       : pool_dim<float, true>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+  return t.row_dtype ? pool_dim<uint16_t, false>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s)
+                     : pool_dim<float, false>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
 }
 
 }  // namespace rs

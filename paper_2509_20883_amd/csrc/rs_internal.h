@@ -54,6 +54,14 @@ constexpr int kRankTile = kBlock * kRankItems;  // 1024
 // Tiles per block of the tile-sum scan.
 constexpr int kScanChunk = 2048;
 
+// A batch of at most kSmallIds ids runs its front end in two launches (unless
+// the table may have to grow), and its pool fills the occurrence list itself.
+constexpr int kSmallIds = 8192;
+// The pool writes the occurrence list of a small batch (its lines stay in L2,
+// so the scattered 4-byte stores cost no memory traffic) and the backward
+// needs no list launch.
+__host__ __device__ inline bool small_batch(int64_t n) { return n <= kSmallIds; }
+
 // Open addressing with linear probing; a lookup reads kProbeBatch
 // consecutive IDMap slots (64 bytes) per round trip.
 constexpr int kProbeBatch = 4;
@@ -320,6 +328,16 @@ hipError_t launch_ids_partition(const int64_t* values, int64_t n, int G, uint64_
 // list position and the hot keys' backward units
 hipError_t launch_compact_insert(const int64_t* values, int64_t n, const TableDev& t, const Work& w, bool occ_lists,
                                  hipEvent_t* ev_compact, hipEvent_t* ev_init, hipEvent_t* ev_occ, hipStream_t s);
+// A small batch (0 < n <= kSmallIds) on a table with room for n new keys: the
+// whole front end up to and including the new rows (publishes the live count
+// as launch_dedup_probe).  occ_lists: a forward; else rows_out [n] and
+// n_inserted (may be null) receive the rows and the number inserted.
+hipError_t launch_small_front(const int64_t* values, int64_t n, const TableDev& t, const Work& w, bool occ_lists,
+                              int64_t* h_live, int64_t tag, int64_t* rows_out, int64_t* n_inserted,
+                              hipEvent_t* ev_front, hipEvent_t* ev_rows, hipStream_t s);
+// occ_ref [n] = -1 and the hot keys' unit counters (in id_ref) = 0: a small
+// batch that took the general front end
+hipError_t launch_clear_refs(const Work& w, int64_t n, hipStream_t s);
 // redo the row reservation of the last scan after the table has grown
 hipError_t launch_rereserve(const Work& w, const TableDev& t, int64_t* h_live, int64_t tag, hipStream_t s);
 hipError_t launch_map_rows(const Work& w, int64_t n, int64_t* rows_out, int64_t* n_inserted, hipStream_t s);
