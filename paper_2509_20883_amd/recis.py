@@ -153,12 +153,21 @@ def _check(st: int):
         raise RecisError(st, lib().rs_last_error().decode())
 
 
-def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+# Per-call costs on the host count for the smallest calls (a kernel there takes
+# 4-9 us): torch.cuda.current_stream() builds a Stream object (2.9 us); the raw
+# handle of the same stream is 0.3 us.  Addresses are passed as plain ints.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+def _stream() -> int:
+    """hipStream_t of the current stream of the current device."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
 def _dev(t: torch.Tensor, dtype: torch.dtype) -> torch.Tensor:
@@ -185,8 +194,7 @@ class Ctx:
 
     def _view(self, ptr: int, count: int, dtype: torch.dtype) -> torch.Tensor:
         off = ptr - self.ws.data_ptr()
-        es = torch.empty(0, dtype=dtype).element_size()
-        return self.ws[off:off + count * es].view(dtype)
+        return self.ws[off:off + count * dtype.itemsize].view(dtype)
 
     def scalars(self) -> torch.Tensor:
         """Device int64[4]: U, inserted, occurrences kept, live rows before."""
@@ -444,7 +452,7 @@ class Table:
         ctx = ctx or Ctx()
         ctx.ensure(self.workspace_bytes(n, bags, pad_len), v.device)
         ctx.keep = (v, o)
-        st = C.c_void_p(stream.cuda_stream) if stream is not None else _stream()
+        st = stream.cuda_stream if stream is not None else _stream()
         _check(lib().lookup_prepare(self.h, _ptr(v), _ptr(o), n, bags, mode, pad_len, C.byref(ctx.c),
                                     int(validate), st))
         return ctx
