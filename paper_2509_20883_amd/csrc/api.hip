@@ -51,7 +51,7 @@ bool padded_mode(int32_t mode) { return mode == RS_POOL_NONE || mode == RS_POOL_
 
 // Workspace layout of one forward: every array sized by the upper bound n.
 struct Layout {
-  size_t occ_word, trec, nrec, srec, pcnt, poff, ptmp, kinfo, inverse, occ_row, occ_pos, unique, useg, rows,
+  size_t occ_word, trec, recres, nrec, srec, pcnt, poff, ptmp, kinfo, inverse, occ_row, occ_pos, unique, useg, rows,
       new_list, id_ref, occ_ref, long_u, long_start, units, bsum, csum, scal, gpart, total;
   int64_t ntiles;
   FrontGeom g;
@@ -73,7 +73,8 @@ Layout make_layout(int64_t n, int dim) {
     return o;
   };
   L.occ_word = take(4 * n1);
-  L.trec = take(sizeof(TileRec) * nrecs);  // also the records' results (int2 each)
+  L.trec = take(sizeof(TileRec) * nrecs);
+  L.recres = take(sizeof(RecRes) * nrecs);
   L.nrec = take(4 * static_cast<size_t>(L.g.nblk));
   L.srec = take(sizeof(TileRec) * nrecs);
   L.pcnt = take(4 * npc);
@@ -105,7 +106,7 @@ Work make_work(void* base, const Layout& L) {
   Work w;
   w.occ_word = reinterpret_cast<uint32_t*>(b + L.occ_word);
   w.trec = reinterpret_cast<TileRec*>(b + L.trec);
-  w.recres = reinterpret_cast<int2*>(b + L.trec);
+  w.recres = reinterpret_cast<RecRes*>(b + L.recres);
   w.nrec = reinterpret_cast<int32_t*>(b + L.nrec);
   w.srec = reinterpret_cast<TileRec*>(b + L.srec);
   w.pcnt = reinterpret_cast<int32_t*>(b + L.pcnt);
@@ -177,7 +178,7 @@ Work make_part_work(void* base, const PartLayout& L, int32_t* inverse) {
   Work w{};
   w.occ_word = reinterpret_cast<uint32_t*>(b + L.occ_word);
   w.trec = reinterpret_cast<TileRec*>(b + L.trec);
-  w.recres = reinterpret_cast<int2*>(b + L.trec);
+  w.recres = reinterpret_cast<RecRes*>(b + L.trec);  // the records themselves are read no more
   w.nrec = reinterpret_cast<int32_t*>(b + L.nrec);
   w.srec = reinterpret_cast<TileRec*>(b + L.srec);
   w.pcnt = reinterpret_cast<int32_t*>(b + L.pcnt);

@@ -23,8 +23,8 @@
 //   k_compact        unique ids in first-occurrence order, occurrence-list
 //                    segments, rows; new keys claim an IDMap slot
 //   k_occ_init       per occurrence: unique id (inverse), row, position in the
-//                    occurrence list, hot-key backward units.  Its other
-//                    blocks write the initial rows of the new keys
+//                    occurrence list.  Its other blocks write the hot keys'
+//                    backward units and the initial rows of the new keys
 // A batch of at most kSmallIds ids on a table that need not grow takes two
 // launches instead of these six: k_small_dedup and k_small_rows.
 #include "device_common.h"
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(NT) void k_tile_dedup(const int64_t* __restrict__ v
       const int sl = ldense[q];
       const unsigned long long e = lkey[sl];
       const unsigned int pr = atomicAdd(&lpc[part_of(e, g.logP)], 1u);
-      rec[nrec + q] = TileRec{e, lmin[sl], (pr << 12) | (lcnt[sl] - 1u)};
+      rec[nrec + q] = TileRec{e, 0u, (pr << 12) | (lcnt[sl] - 1u)};
       lmin[sl] = nrec + static_cast<unsigned int>(q);
     }
     __syncthreads();
@@ -288,6 +288,7 @@ __global__ __launch_bounds__(NT) void k_tile_dedup(const int64_t* __restrict__ v
   }
   __syncthreads();
   TileRec* srt = w.srec + blk * g.rcap;
+  const unsigned int src0 = static_cast<unsigned int>(blk * g.rcap);
   constexpr int U8 = 8;  // records in flight per thread
   // Record j goes to position lpc[partition] + its rank in the partition.
   // A block of at most kStageChunks chunks of SLOTS records assembles each
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(NT) void k_tile_dedup(const int64_t* __restrict__ v
         const unsigned int j = j0 + u * NT;
         if (j >= nrec) continue;
         const unsigned int o = lpc[part_of(r[u].key, g.logP)] + (r[u].meta >> 12);
-        const TileRec x{r[u].key, r[u].tmin, (j << 12) | (r[u].meta & 0xFFFu)};
+        const TileRec x{r[u].key, src0 + j, r[u].meta & 0xFFFu};
         if (!staged) srt[o] = x;
         else if (o >= o0 && o < o1) lbuf[o - o0] = x;
       }
@@ -348,21 +349,20 @@ __device__ inline int64_t resolve_probe(const TableDev& t, unsigned long long e,
 
 // The partition's records are read from every dedup block's
 // partition-ordered copy (segment b: cnt[b] records at off[b]).  A key's
-// index is the position of its first record (the one holding its first
-// position): for a lookup its tile-order position, so the key info of a
-// tile's first records lies together, in the order in which the
-// first-occurrence sums and the compaction read and write it, and the info
-// of a key seen once lies beside its ids' records; for the ids partition
-// (no key info) its position in the partition-ordered copy, whose entry
-// there holds the key.
+// index is the smallest place in tile order of its records: that record holds
+// its first position (the records of a dedup block, and the blocks, are in
+// first-position order).  Every record gets one 16-byte result at its place;
+// the first records' results carry the key's count and row, in the order in
+// which the first-occurrence sums and the compaction read them (a separate
+// 32-byte key entry per key beside 8-byte results cost RECRES_FIG).
 // A partition of at most kPartSlots records is done in one pass with each
 // thread's records in registers (its distinct keys always fit the table);
 // a larger one in sweeps of at most kPartSweep records by a hash of the key,
 // and if a sweep's keys do not fit (a skewed hash) the partition starts
 // again with twice as many sweeps.
-__device__ inline void probe_store_keys(const TableDev& t, const Work& w, int64_t n, int d, const short* cdense,
-                                        const unsigned long long* ckey, const unsigned long long* cfp,
-                                        const unsigned int* ccnt) {
+
+// IDMap rows of the d keys listed in cdense; a key's row replaces it in the table.
+__device__ inline void probe_keys(const TableDev& t, int d, const short* cdense, unsigned long long* ckey) {
   constexpr int NT = kPartThreads;
   constexpr int KP = 4;  // keys per thread per round: their probe batches in flight together
   for (int q0 = 0; q0 < d; q0 += KP * NT) {
@@ -376,26 +376,12 @@ __device__ inline void probe_store_keys(const TableDev& t, const Work& w, int64_
       sl[u] = q < d ? cdense[q] : -1;
       e[u] = sl[u] >= 0 ? ckey[sl[u]] : kEncEmpty;
       h[u] = sl[u] >= 0 ? (idmap_hash(e[u]) & t.cap_mask) : 0;  // idle lanes read one shared line
-      if (t.slots) {
 #pragma unroll
-        for (int k = 0; k < kProbeBatch; ++k) pb[u][k] = t.slots[(h[u] + k) & t.cap_mask];
-      }
+      for (int k = 0; k < kProbeBatch; ++k) pb[u][k] = t.slots[(h[u] + k) & t.cap_mask];
     }
 #pragma unroll
-    for (int u = 0; u < KP; ++u) {
-      if (sl[u] < 0) continue;
-      const unsigned int kidx = static_cast<unsigned int>(cfp[sl[u]]);
-      {
-        KeyInfo ki;
-        ki.row = t.slots ? resolve_probe(t, e[u], h[u], pb[u]) : 0;  // no table: nothing to probe
-        ki.key = static_cast<long long>(e[u] ^ kSign);
-        ki.count = static_cast<int>(ccnt[sl[u]]);
-        ki.uid = -1;
-        ki.start = 0;
-        ki.long_idx = -1;
-        w.kinfo[kidx] = ki;
-      }
-    }
+    for (int u = 0; u < KP; ++u)
+      if (sl[u] >= 0) ckey[sl[u]] = static_cast<unsigned long long>(resolve_probe(t, e[u], h[u], pb[u]));
   }
 }
 
@@ -417,9 +403,7 @@ __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w,
   constexpr int kMaxSweeps = 1 << 10;
   constexpr int BPT = (kMaxDedupBlocks + NT - 1) / NT;
   __shared__ unsigned long long ckey[S];
-  // (first position << 32 | position of the record holding it): the minimum
-  // over the key's records gives the key's first position and its key index
-  __shared__ unsigned long long cfp[S];
+  __shared__ unsigned int cfp[S];  // the key's index: the smallest place of its records
   __shared__ unsigned int ccnt[S];
   __shared__ short cdense[S];  // dense index -> slot
   __shared__ int cpre[kMaxDedupBlocks];   // exclusive prefix of the segment sizes
@@ -449,7 +433,7 @@ __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w,
   }
   for (int q = tid; q < S; q += NT) {
     ckey[q] = kEncEmpty;
-    cfp[q] = ~0ull;
+    cfp[q] = ~0u;
     ccnt[q] = 0u;
   }
   if (tid == 0) ovf = 0;
@@ -483,10 +467,17 @@ __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w,
     return d;
   };
 
-  // the key index a record would give its key (see above)
-  auto rec_index = [&](int pos, const TileRec& x) {
-    return w.kinfo ? static_cast<unsigned int>((pos / g.rcap) * g.rcap + (x.meta >> 12))
-                   : static_cast<unsigned int>(pos);
+  const bool lookup = w.kinfo != nullptr;  // else the ids partition
+  // record of key `key` at place src, entered at LDS slot sl, rb occurrences
+  // of its key before it (its key's row already in the table)
+  auto result = [&](unsigned int src, unsigned long long key, int sl, unsigned int rb) {
+    const unsigned int kidx = cfp[sl];
+    const bool first = kidx == src;
+    RecRes r;
+    r.x = static_cast<int>(first && lookup ? ccnt[sl] : kidx);
+    r.y = rb | (first ? kRecFirst : 0u);
+    r.v = lookup ? static_cast<long long>(ckey[sl]) : static_cast<long long>(key ^ kSign);
+    w.recres[src] = r;
   };
   bool fresh = true;  // the LDS table is clear
   if (nr <= NT * K) {
@@ -510,61 +501,70 @@ __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w,
       sl[k] = lds_insert(ckey, x[k].key, part_hash(x[k].key));
       if (sl[k] < 0) {
         ovf = 1;
-        pos[k] = -1;
         continue;
       }
-      atomicMin(&cfp[sl[k]], (static_cast<unsigned long long>(x[k].tmin) << 32) | rec_index(pos[k], x[k]));
-      rb[k] = atomicAdd(&ccnt[sl[k]], (x[k].meta & 0xFFFu) + 1u);
+      atomicMin(&cfp[sl[k]], x[k].src);
+      rb[k] = atomicAdd(&ccnt[sl[k]], x[k].meta + 1u);
     }
     __syncthreads();
     if (!ovf) {
-      if (w.kinfo) {  // null (ids partition): no key info, no probe
+      if (lookup) {
         const int d = dense_list();
-        probe_store_keys(t, w, n, d, cdense, ckey, cfp, ccnt);
+        probe_keys(t, d, cdense, ckey);
+        __syncthreads();
       }
 #pragma unroll
-      for (int k = 0; k < K; ++k) {
-        if (pos[k] < 0) continue;
-        const int64_t src = (static_cast<int64_t>(pos[k]) / g.rcap) * g.rcap + (x[k].meta >> 12);
-        const unsigned int kidx = static_cast<unsigned int>(cfp[sl[k]]);
-        // the key's first record is the one whose index is its key index
-        const unsigned int fl = kidx == rec_index(pos[k], x[k]) ? kRecFirst : 0u;
-        w.recres[src] = make_int2(static_cast<int>(kidx), static_cast<int>(rb[k] | fl));
-      }
+      for (int k = 0; k < K; ++k)
+        if (sl[k] >= 0) result(x[k].src, x[k].key, sl[k], rb[k]);
       return;
     }
     fresh = false;
     __syncthreads();  // every thread has read ovf before the sweeps reset it
   }
 
-  // sweeps (rare: a partition far above the average size)
+  // sweeps: a partition above the register pass (ids that hardly repeat, or a
+  // skewed hash).  Sweep s takes the keys whose 20 hash bits mod nsw are s (a
+  // 32-bit remainder).  KS records per thread and round: their loads are in
+  // flight together.
+  constexpr int KS = 4;
   int nsw = min((nr + kPartSweep - 1) / kPartSweep, kMaxSweeps);
+  auto sweep_of = [&](uint64_t h) {
+    return static_cast<int>((static_cast<uint32_t>(h) & 0xFFFFFu) % static_cast<uint32_t>(nsw));
+  };
   int s = 0;
   while (s < nsw) {
     if (!fresh) {
       for (int q = tid; q < S; q += NT) {
         ckey[q] = kEncEmpty;
-        cfp[q] = ~0ull;
+        cfp[q] = ~0u;
         ccnt[q] = 0u;
       }
     }
     fresh = false;
     if (tid == 0) ovf = 0;
     __syncthreads();
-    for (int fr = tid; fr < nr; fr += NT) {
-      const int pos = rec_pos(fr);
-      const TileRec x = w.srec[pos];
-      const uint64_t h = part_hash(x.key);
-      if (static_cast<int>((h & 0xFFFFFull) % static_cast<uint64_t>(nsw)) != s) continue;
-      const int sl = lds_insert(ckey, x.key, h);
-      if (sl < 0) {
-        ovf = 1;
-        continue;
+    for (int f0 = tid; f0 < nr; f0 += KS * NT) {
+      int pos[KS];
+      TileRec x[KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        pos[k] = f0 + k * NT < nr ? rec_pos(f0 + k * NT) : -1;
+        if (pos[k] >= 0) x[k] = w.srec[pos[k]];
       }
-      atomicMin(&cfp[sl], (static_cast<unsigned long long>(x.tmin) << 32) | rec_index(pos, x));
-      const unsigned int rb = atomicAdd(&ccnt[sl], (x.meta & 0xFFFu) + 1u);
-      w.ptmp[pos] = make_int2(static_cast<int>(((x.meta >> 12) << 12) | static_cast<unsigned int>(sl)),
-                              static_cast<int>(rb));
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        if (pos[k] < 0) continue;
+        const uint64_t h = part_hash(x[k].key);
+        if (sweep_of(h) != s) continue;
+        const int sl = lds_insert(ckey, x[k].key, h);
+        if (sl < 0) {
+          ovf = 1;
+          continue;
+        }
+        atomicMin(&cfp[sl], x[k].src);
+        const unsigned int rb = atomicAdd(&ccnt[sl], x[k].meta + 1u);
+        w.ptmp[pos[k]] = make_int2(sl, static_cast<int>(rb));
+      }
     }
     __syncthreads();
     if (ovf) {
@@ -577,20 +577,27 @@ __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w,
       s = 0;
       continue;
     }
-    if (w.kinfo) {
+    if (lookup) {
       const int d = dense_list();
-      probe_store_keys(t, w, n, d, cdense, ckey, cfp, ccnt);
+      probe_keys(t, d, cdense, ckey);
+      __syncthreads();
     }
-    for (int fr = tid; fr < nr; fr += NT) {
-      const int pos = rec_pos(fr);
-      const uint64_t h = part_hash(w.srec[pos].key);
-      if (static_cast<int>((h & 0xFFFFFull) % static_cast<uint64_t>(nsw)) != s) continue;
-      const int2 tp = w.ptmp[pos];
-      const int64_t src = (static_cast<int64_t>(pos) / g.rcap) * g.rcap + (static_cast<uint32_t>(tp.x) >> 12);
-      const unsigned int kidx = static_cast<unsigned int>(cfp[tp.x & 0xFFF]);
-      const unsigned int ix = w.kinfo ? static_cast<unsigned int>(src) : static_cast<unsigned int>(pos);
-      const unsigned int fl = kidx == ix ? kRecFirst : 0u;
-      w.recres[src] = make_int2(static_cast<int>(kidx), static_cast<int>(static_cast<unsigned int>(tp.y) | fl));
+    for (int f0 = tid; f0 < nr; f0 += KS * NT) {
+      int pos[KS];
+      TileRec x[KS];
+      int2 tp[KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        pos[k] = f0 + k * NT < nr ? rec_pos(f0 + k * NT) : -1;
+        if (pos[k] >= 0) {
+          x[k] = w.srec[pos[k]];
+          tp[k] = w.ptmp[pos[k]];  // unset, or another sweep's, where the record is another sweep's
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+        if (pos[k] >= 0 && sweep_of(part_hash(x[k].key)) == s)
+          result(x[k].src, x[k].key, tp[k].x, static_cast<unsigned int>(tp[k].y));
     }
     ++s;
     __syncthreads();  // the next sweep clears the LDS
@@ -614,68 +621,80 @@ __device__ inline void load4(const int32_t* __restrict__ p, int64_t i0, int64_t 
   }
 }
 
-// Key info of key index k (k >= 0), or of index 0 for an idle lane (read,
-// never used: every load of a step is issued before its results are waited for).
-__device__ inline KeyInfo key_info(const Work& w, int k) {
-  return w.kinfo[min(max(k, 0), static_cast<int>(w.nkeyidx - 1))];
+// Record tile rt: its dedup block, and the place of its first record slot.
+struct RecTile {
+  uint32_t blk, at, left;  // left: records of the dedup block from `at` on (<= 0 as a signed number: none)
+};
+
+__device__ inline RecTile rec_tile(const Work& w, uint32_t rt) {
+  const uint32_t per = static_cast<uint32_t>(w.g.rcap / kRankTile);  // record tiles per dedup block
+  RecTile x;
+  x.blk = rt / per;  // 32 bits: places are below 2^28
+  const uint32_t r0 = (rt - x.blk * per) * kRankTile;
+  x.at = x.blk * static_cast<uint32_t>(w.g.rcap) + r0;
+  x.left = static_cast<uint32_t>(w.nrec[x.blk]) - r0;
+  return x;
 }
 
-// The first records of record tile rt (4 record slots per thread): the key
-// index of each first record (a key's first record is its only one that is
-// counted), or -1.  Records past the dedup block's count are not read.
-__device__ inline void first_records(const Work& w, int64_t rt, int (&f)[4]) {
-  const int64_t per = w.g.rcap / kRankTile;  // record tiles per dedup block
-  const int64_t blk = rt / per;
-  const int64_t r0 = (rt % per) * kRankTile + static_cast<int64_t>(threadIdx.x) * 4;
-  const int64_t nr = w.nrec[blk];
-  const int4 a = *reinterpret_cast<const int4*>(w.recres + blk * w.g.rcap + r0);  // 2 records
-  const int4 b = *reinterpret_cast<const int4*>(w.recres + blk * w.g.rcap + r0 + 2);
-  const int x[4] = {a.x, a.z, b.x, b.z}, y[4] = {a.y, a.w, b.y, b.w};
+// The tile lies wholly past its dedup block's records (a block's record slots
+// are sized for its ids, and distinct keys are fewer).
+__device__ inline bool empty_tile(const RecTile& x) { return static_cast<int32_t>(x.left) <= 0; }
+
+// The results of 4 record slots per thread (a key's first record is its only
+// one that is counted); first[k]: slot k holds a first record.
+__device__ inline void load_results(const Work& w, const RecTile& x, RecRes (&r)[4], bool (&first)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) r[k] = w.recres[x.at + threadIdx.x * 4 + k];
 #pragma unroll
   for (int k = 0; k < 4; ++k)
-    f[k] = r0 + k < nr && (static_cast<uint32_t>(y[k]) & kRecFirst) ? x[k] : -1;
+    first[k] = static_cast<int32_t>(threadIdx.x * 4 + k) < static_cast<int32_t>(x.left) && (r[k].y & kRecFirst);
 }
 
-// Record tile rt lies wholly past its dedup block's records (a block's record
-// slots are sized for its ids, and distinct keys are fewer).
-__device__ inline bool empty_record_tile(const Work& w, int64_t rt) {
-  const int64_t per = w.g.rcap / kRankTile;
-  return (rt % per) * kRankTile >= w.nrec[rt / per];
+// What a tile's four slots of a thread add to the sums: keys, their counts,
+// keys not found, hot keys, hot-key units.
+__device__ inline void sum_firsts(const RecRes (&r)[4], const bool (&first)[4], int (&v)[5]) {
+#pragma unroll
+  for (int a = 0; a < 5; ++a) v[a] = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (!first[k]) continue;
+    v[0] += 1;
+    v[1] += r[k].x;
+    v[2] += r[k].v < 0;
+    if (r[k].x > kLong) {
+      v[3] += 1;
+      v[4] += unit_count(r[k].x);
+    }
+  }
 }
 
-// Per record tile: sums over its first records (keys, their counts, keys not
-// found, hot keys, hot-key units).  Record tiles in block-major order list
-// the keys in the order of their first positions.
+// Per record tile: sums over its first records.  Record tiles in block-major
+// order list the keys in the order of their first positions.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_first_sums(Work w) {
-  __shared__ int sh[NT / kWave + 1][5];
-  if (empty_record_tile(w, blockIdx.x)) {  // block-uniform
+  __shared__ int sh[NT / kWave][5];
+  const RecTile x = rec_tile(w, blockIdx.x);
+  if (empty_tile(x)) {  // block-uniform
     if (threadIdx.x < 5) w.bsum[threadIdx.x * w.ntiles + blockIdx.x] = 0;
     return;
   }
-  int f[4];
-  first_records(w, blockIdx.x, f);
-  KeyInfo ki[4];
+  RecRes r[4];
+  bool first[4];
+  load_results(w, x, r, first);
+  int v[5];
+  sum_firsts(r, first, v);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) ki[k] = key_info(w, f[k]);
-  int cf = 0, c = 0, nw = 0, nl = 0, nu = 0;
+  for (int a = 0; a < 5; ++a) v[a] = wave_sum(v[a]);
+  if ((threadIdx.x & (kWave - 1)) == 0) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if (f[k] < 0) continue;
-    cf += 1;
-    c += ki[k].count;
-    nw += ki[k].row < 0;
-    if (ki[k].count > kLong) {
-      nl += 1;
-      nu += unit_count(ki[k].count);
-    }
+    for (int a = 0; a < 5; ++a) sh[threadIdx.x / kWave][a] = v[a];
   }
-  const int v[5] = {cf, c, nw, nl, nu};
-  int ex[5], tot[5];
-  block_excl_scan5<NT>(v, ex, tot, sh);
-  if (threadIdx.x == 0) {
+  __syncthreads();
+  if (threadIdx.x < 5) {
+    int tot = 0;
 #pragma unroll
-    for (int a = 0; a < 5; ++a) w.bsum[a * w.ntiles + blockIdx.x] = tot[a];
+    for (int q = 0; q < NT / kWave; ++q) tot += sh[q][threadIdx.x];
+    w.bsum[threadIdx.x * w.ntiles + blockIdx.x] = tot;
   }
 }
 
@@ -888,32 +907,22 @@ __global__ __launch_bounds__(NT) void k_compact(TableDev t, Work w) {
   __shared__ int sh[NT / kWave + 1][5];
   const int b = blockIdx.x;
   if (blockIdx.x == 0 && threadIdx.x == 0 && w.scal[kCTrunc]) atomicOr(reinterpret_cast<int*>(&t.scal[kTErr]), kErrFull);
-  if (empty_record_tile(w, b)) return;  // block-uniform: no keys, nothing to write
+  const RecTile x = rec_tile(w, b);
+  if (empty_tile(x)) return;  // block-uniform: no keys, nothing to write
   int pre[5];  // the record tile's exclusive prefixes (keys, count, new, hot, units)
   const int64_t nch = (static_cast<int64_t>(gridDim.x) + kScanChunk - 1) / kScanChunk;
 #pragma unroll
   for (int a = 0; a < 5; ++a) pre[a] = w.bsum[a * w.ntiles + b] + w.csum[a * nch + b / kScanChunk];
-  int f[4];
-  first_records(w, b, f);
-  KeyInfo ki[4];
+  RecRes r[4];
+  bool first[4];
+  load_results(w, x, r, first);
+  unsigned long long ek[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) ki[k] = key_info(w, f[k]);  // all four reads in flight together
-  int cf = 0, cc = 0, cn = 0, cl = 0, cu = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if (f[k] < 0) continue;
-    cf += 1;
-    cc += ki[k].count;
-    cn += ki[k].row < 0;
-    if (ki[k].count > kLong) {
-      cl += 1;
-      cu += unit_count(ki[k].count);
-    }
-  }
+  for (int k = 0; k < 4; ++k) ek[k] = w.trec[x.at + threadIdx.x * 4 + k].key;  // all reads in flight together
   // the tile's keys get consecutive unique ids, segments, rows of new keys,
   // hot-key indices and backward units
-  const int v[5] = {cf, cc, cn, cl, cu};
-  int ex[5], tot[5];
+  int v[5], ex[5], tot[5];
+  sum_firsts(r, first, v);
   block_excl_scan5<NT>(v, ex, tot, sh);
   int uid = pre[0] + ex[0];
   int start = pre[1] + ex[1];
@@ -925,21 +934,20 @@ __global__ __launch_bounds__(NT) void k_compact(TableDev t, Work w) {
   const int64_t ftop = w.scal[kCFreeTop], ftake = w.scal[kCFreeTake];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    if (f[k] < 0) continue;
-    const int c = ki[k].count;
-    const int64_t key = ki[k].key;
+    if (!first[k]) continue;
+    const int c = r[k].x;
+    const int64_t key = static_cast<int64_t>(ek[k] ^ kSign);
     w.unique[uid] = key;
-    int li = -1;
     if (c > kLong) {
-      li = lnext++;
-      w.long_u[li] = uid;
-      w.long_start[li] = unext;
+      w.long_u[lnext] = uid;
+      w.long_start[lnext] = unext;
+      ++lnext;
       unext += unit_count(c);
     }
-    int64_t row = ki[k].row;
+    int64_t row = r[k].v;
     if (row < 0) {
       if (nr < inserted) {
-        const int64_t slot = idmap_claim(t, static_cast<unsigned long long>(key) ^ kSign);
+        const int64_t slot = idmap_claim(t, ek[k]);
         if (slot >= 0) {
           // the first `ftake` new keys take free rows from the top of the stack
           row = nr < ftake ? t.free_rows[ftop - 1 - nr] : live0 + (nr - ftake);
@@ -957,12 +965,7 @@ __global__ __launch_bounds__(NT) void k_compact(TableDev t, Work w) {
     }
     w.rows[uid] = row;
     w.useg[uid] = Seg{row, start, c};
-    KeyInfo o = ki[k];
-    o.row = row;
-    o.uid = uid;
-    o.start = start;
-    o.long_idx = li;
-    w.kinfo[f[k]] = o;
+    w.kinfo[x.at + threadIdx.x * 4 + k] = KeyInfo{row, uid, start};
     ++uid;
     start += c;
   }
@@ -1036,43 +1039,40 @@ __device__ inline void init_rows(const TableDev& t, const Work& w, int64_t blk, 
 // The per-occurrence pass: inverse[i] = unique id of occurrence i (-1 for a
 // rejected key).  For a forward (OCC) it also writes each occurrence's row
 // and its position in the occurrence list (the key's segment start + the
-// record's rank base + the rank inside the tile), and the descriptor of
-// every backward unit of a hot key.
+// occurrences of the key before the record + the rank inside the tile).
 template <bool OCC>
-__device__ inline void occ_pass(const Work& w, int64_t n, int64_t blk) {
-  const int64_t i0 = (blk * kBlock + threadIdx.x) * 4;
+__device__ inline void occ_pass(const Work& w, int64_t n, uint32_t blk) {
+  const int64_t i0 = (static_cast<int64_t>(blk) * kBlock + threadIdx.x) * 4;
   if (i0 >= n) return;
-  const FrontGeom g = w.g;
+  // a block's kBlock * 4 ids lie in one dedup tile: its records' place is the same for all
+  static_assert(kDedupTile % (kBlock * 4) == 0, "a block's ids share a dedup tile");
+  const uint32_t tile = blk / (kDedupTile / (kBlock * 4));
+  const uint32_t base = tile / static_cast<uint32_t>(w.g.R) * static_cast<uint32_t>(w.g.rcap);
   int ow[4];
   load4(reinterpret_cast<const int32_t*>(w.occ_word), i0, n, ow);  // -1 = kOccRejected past n
-  int2 rr[4];
+  uint2 rr[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const uint32_t o = static_cast<uint32_t>(ow[k]);
-    const int64_t src = o == kOccRejected ? 0 : ((i0 + k) >> kDedupTileLog2) / g.R * g.rcap + (o >> 12);
-    rr[k] = w.recres[src];  // all in flight together
+    rr[k] = *reinterpret_cast<const uint2*>(&w.recres[o == kOccRejected ? 0u : base + (o >> 12)]);  // x, y: all in flight together
   }
   KeyInfo a[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) a[k] = key_info(w, rr[k].x);
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t o = static_cast<uint32_t>(ow[k]);
+    const uint32_t kidx = rr[k].y & kRecFirst ? base + (o >> 12) : rr[k].x;
+    // in range also where an overflowed partition left no result
+    a[k] = w.kinfo[o == kOccRejected ? 0u : min(kidx, static_cast<uint32_t>(w.nkeyidx - 1))];
+  }
   int pos[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const uint32_t o = static_cast<uint32_t>(ow[k]);
+    pos[k] = a[k].start + static_cast<int>(rr[k].y & ~kRecFirst) + static_cast<int>(o & 0xFFFu);
     if (o == kOccRejected) {
       a[k].row = -1;
       a[k].uid = -1;
       pos[k] = -1;
-      continue;
-    }
-    const int rk = static_cast<int>(static_cast<uint32_t>(rr[k].y) & ~kRecFirst) + static_cast<int>(o & 0xFFFu);
-    pos[k] = a[k].start + rk;
-    if (OCC && a[k].long_idx >= 0) {
-      const int sh = unit_shift(a[k].count);
-      const int usz = kUnit << sh;
-      if ((rk & (usz - 1)) == 0)
-        w.units[w.long_start[a[k].long_idx] + (rk >> (kUnitLog2 + sh))] =
-            Unit{a[k].long_idx, pos[k], min(pos[k] + usz, a[k].start + a[k].count), 0};
     }
   }
   if (i0 + 4 <= n) {
@@ -1095,14 +1095,31 @@ __device__ inline void occ_pass(const Work& w, int64_t n, int64_t blk) {
   }
 }
 
+// Backward units of the hot keys, one per thread: the hot key of unit y is the
+// last one whose first unit is <= y.
+__device__ inline void write_unit(const Work& w, int64_t y) {
+  if (y >= w.scal[kCNUnits]) return;
+  int lo = 0, hi = static_cast<int>(w.scal[kCNLong]);
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (w.long_start[mid] <= y) lo = mid;
+    else hi = mid;
+  }
+  const Seg sg = w.useg[w.long_u[lo]];
+  const int usz = kUnit << unit_shift(sg.count), j = static_cast<int>(y) - w.long_start[lo];
+  w.units[y] = Unit{lo, sg.start + j * usz, sg.start + min((j + 1) * usz, sg.count), 0};
+}
+
 // The last pass of a lookup: blocks [0, occ_blocks) run the per-occurrence
-// pass, the others write the rows of the inserted keys (both only need the
-// compaction, so they share one launch).
+// pass, the next unit_blocks write the hot keys' units, the others the rows of
+// the inserted keys (all only need the compaction, so they share one launch).
 template <bool OCC>
-__global__ __launch_bounds__(kBlock) void k_occ_init(TableDev t, Work w, int64_t n, int64_t occ_blocks) {
-  const int64_t b = blockIdx.x;
+__global__ __launch_bounds__(kBlock) void k_occ_init(TableDev t, Work w, int64_t n, uint32_t occ_blocks,
+                                                     uint32_t unit_blocks) {
+  const uint32_t b = blockIdx.x;
   if (b < occ_blocks) occ_pass<OCC>(w, n, b);
-  else init_rows(t, w, b - occ_blocks, static_cast<int64_t>(gridDim.x) - occ_blocks);
+  else if (b - occ_blocks < unit_blocks) write_unit(w, static_cast<int64_t>(b - occ_blocks) * kBlock + threadIdx.x);
+  else init_rows(t, w, b - occ_blocks - unit_blocks, gridDim.x - occ_blocks - unit_blocks);
 }
 
 hipError_t launch_compact_insert(const int64_t* values, int64_t n, const TableDev& t, const Work& w, bool occ_lists,
@@ -1116,10 +1133,11 @@ hipError_t launch_compact_insert(const int64_t* values, int64_t n, const TableDe
   // occurrence events both bracket it)
   if (ev_init && ev_init[0]) (void)hipEventRecord(ev_init[0], s);
   if (ev_occ && ev_occ[0]) (void)hipEventRecord(ev_occ[0], s);
-  const int64_t ob = grid_for(n, kBlock * 4, 1ll << 31);
-  const int64_t ib = grid_for(n, kBlock / 16, 8192);
-  if (occ_lists) k_occ_init<true><<<static_cast<unsigned>(ob + ib), kBlock, 0, s>>>(t, w, n, ob);
-  else k_occ_init<false><<<static_cast<unsigned>(ob + ib), kBlock, 0, s>>>(t, w, n, ob);
+  const unsigned ob = grid_for(n, kBlock * 4, 1ll << 31);
+  const unsigned ib = grid_for(n, kBlock / 16, 8192);
+  const unsigned ub = occ_lists ? grid_for(2 * (n / kUnit) + 2, kBlock) : 0u;
+  if (occ_lists) k_occ_init<true><<<static_cast<unsigned>(ob + ub + ib), kBlock, 0, s>>>(t, w, n, ob, ub);
+  else k_occ_init<false><<<static_cast<unsigned>(ob + ib), kBlock, 0, s>>>(t, w, n, ob, 0u);
   if (ev_occ && ev_occ[1]) (void)hipEventRecord(ev_occ[1], s);
   if (ev_init && ev_init[1]) (void)hipEventRecord(ev_init[1], s);
   return hipGetLastError();

@@ -26,10 +26,12 @@
 
 namespace rs {
 
-__device__ inline uint32_t owner_of(int64_t key, uint64_t seed, uint32_t G, uint32_t gmask) {
+// h mod G with inv = floor((2^64 - 1) / G): the quotient estimate is the
+// quotient or one less (Barrett 1986), a 64-bit division less per key.
+__device__ inline uint32_t owner_of(int64_t key, uint64_t seed, uint32_t G, uint64_t inv) {
   const uint64_t h = mix64(static_cast<uint64_t>(key) ^ seed);
-  // G a power of two: the mask is the same residue
-  return gmask ? static_cast<uint32_t>(h & gmask) : static_cast<uint32_t>(h % G);
+  const uint64_t r = h - __umul64hi(h, inv) * G;
+  return static_cast<uint32_t>(r >= G ? r - G : r);
 }
 
 OwnerGeom owner_geom(int64_t n, int G) {
@@ -48,7 +50,7 @@ OwnerGeom owner_geom(int64_t n, int G) {
   og.nch = (og.len + kScanChunk - 1) / kScanChunk;
   og.nbits = 0;
   while ((1 << og.nbits) < G) ++og.nbits;
-  og.gmask = (G & (G - 1)) == 0 ? static_cast<uint32_t>(G - 1) : 0u;
+  og.inv = ~0ull / static_cast<uint64_t>(G);
   return og;
 }
 
@@ -57,25 +59,21 @@ OwnerGeom owner_geom(int64_t n, int G) {
 // the order of the keys' first positions.  "Position" b below is a record
 // slot: record tile b / kRankTile, slot b % kRankTile; item k of thread t is
 // slot k * kBlock + t (item-major, then thread: ascending record order).
-// f[k]: the key index of a first record, else -1; v[k]: its key (from the
-// partition-ordered copy, whose entry at the key index is that record).
+// f[k]: the key index of a first record (its place), else -1; v[k]: its key.
 __device__ inline void load_tile(const Work& w, int64_t b, int (&f)[kRankItems], int64_t (&v)[kRankItems]) {
-  const int64_t per = w.g.rcap / kRankTile;
-  const int64_t rt = b / kRankTile;
-  const int64_t blk = rt / per;
-  const int64_t base = blk * w.g.rcap + (rt % per) * kRankTile;
-  const int64_t nr = blk * w.g.rcap + w.nrec[blk];
-  int2 r[kRankItems];
+  const uint32_t per = static_cast<uint32_t>(w.g.rcap / kRankTile);
+  const uint32_t rt = static_cast<uint32_t>(b / kRankTile);
+  const uint32_t blk = rt / per;
+  const uint32_t base = blk * static_cast<uint32_t>(w.g.rcap) + (rt - blk * per) * kRankTile;
+  const uint32_t nr = blk * static_cast<uint32_t>(w.g.rcap) + static_cast<uint32_t>(w.nrec[blk]);
+  RecRes r[kRankItems];
 #pragma unroll
   for (int k = 0; k < kRankItems; ++k) r[k] = w.recres[base + k * kBlock + threadIdx.x];
 #pragma unroll
   for (int k = 0; k < kRankItems; ++k) {
-    const int64_t j = base + k * kBlock + threadIdx.x;
-    f[k] = j < nr && (static_cast<uint32_t>(r[k].y) & kRecFirst) ? r[k].x : -1;
+    f[k] = base + k * kBlock + threadIdx.x < nr && (r[k].y & kRecFirst) ? r[k].x : -1;
+    v[k] = r[k].v;
   }
-#pragma unroll
-  for (int k = 0; k < kRankItems; ++k)
-    v[k] = f[k] >= 0 ? static_cast<int64_t>(w.srec[f[k]].key ^ kSign) : 0;  // all in flight together
 }
 
 __global__ __launch_bounds__(kBlock) void k_owner_hist(Work w, int64_t n, int G, uint64_t seed, OwnerGeom og,
@@ -92,7 +90,7 @@ __global__ __launch_bounds__(kBlock) void k_owner_hist(Work w, int64_t n, int G,
     load_tile(w, b, f, v);
 #pragma unroll
     for (int k = 0; k < kRankItems; ++k)
-      if (f[k] >= 0) atomicAdd(&lh[owner_of(v[k], seed, G, og.gmask)], 1);
+      if (f[k] >= 0) atomicAdd(&lh[owner_of(v[k], seed, G, og.inv)], 1);
   }
   __syncthreads();
   for (int q = threadIdx.x; q < G; q += kBlock) hist[static_cast<int64_t>(q) * og.nb + blockIdx.x] = lh[q];
@@ -235,7 +233,7 @@ __global__ __launch_bounds__(kBlock) void k_owner_scatter(Work w, int64_t n, int
     load_tile(w, b, f, v);
     uint32_t own[kRankItems];
 #pragma unroll
-    for (int k = 0; k < kRankItems; ++k) own[k] = f[k] >= 0 ? owner_of(v[k], seed, G, og.gmask) : 0u;
+    for (int k = 0; k < kRankItems; ++k) own[k] = f[k] >= 0 ? owner_of(v[k], seed, G, og.inv) : 0u;
     // item k of every thread, in position order: waves 0..NW-1, lanes 0..63
 #pragma unroll
     for (int k = 0; k < kRankItems; ++k) {
@@ -273,7 +271,9 @@ __global__ __launch_bounds__(kBlock) void k_owner_scatter(Work w, int64_t n, int
 __global__ __launch_bounds__(kBlock) void k_ids_inverse(Work w, const int32_t* __restrict__ kslot, int64_t n) {
   const int64_t i0 = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * 4;
   if (i0 >= n) return;
-  const FrontGeom g = w.g;
+  static_assert(kDedupTile % (kBlock * 4) == 0, "a block's ids share a dedup tile");
+  const uint32_t base = blockIdx.x / (kDedupTile / (kBlock * 4)) / static_cast<uint32_t>(w.g.R) *
+                        static_cast<uint32_t>(w.g.rcap);
   uint32_t o[4];
   if (i0 + 4 <= n) {
     const uint4 a = *reinterpret_cast<const uint4*>(w.occ_word + i0);
@@ -289,13 +289,12 @@ __global__ __launch_bounds__(kBlock) void k_ids_inverse(Work w, const int32_t* _
 #pragma unroll
   for (int k = 0; k < 4; ++k) {  // all four record reads in flight together
     const bool rej = o[k] == kOccRejected;
-    const int64_t src = rej ? 0 : ((i0 + k) >> kDedupTileLog2) / g.R * g.rcap + (o[k] >> 12);
-    const int x = w.recres[src].x;
+    const int x = w.recres[rej ? 0u : base + (o[k] >> 12)].x;
     kid[k] = rej ? -1 : x;
   }
   int pos[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) pos[k] = kid[k] < 0 ? -1 : kslot[kid[k]];
+  for (int k = 0; k < 4; ++k) pos[k] = kid[k] < 0 ? -1 : kslot[min(kid[k], static_cast<int>(w.nkeyidx - 1))];
   if (i0 + 4 <= n) {
     *reinterpret_cast<int4*>(w.inverse + i0) = make_int4(pos[0], pos[1], pos[2], pos[3]);
   } else {

@@ -141,7 +141,7 @@ struct OwnerGeom {
   int64_t len;    // G * nb per-(shard, block) counts
   int64_t nch;    // scan chunks of the counts (<= kScanChunk)
   int nbits;      // bits of an owner index
-  uint32_t gmask; // G - 1 if G is a power of two, else 0
+  uint64_t inv;   // floor((2^64 - 1) / G)
 };
 
 __host__ __device__ inline uint64_t mix64(uint64_t z) {
@@ -207,23 +207,32 @@ struct FrontGeom {
 // in the order of the keys' first positions in the tile (so a block's
 // records, tile after tile, are in first-position order), with meta = (rank
 // of the record among its block's records of the same partition) << 12 |
-// (count - 1); the block then copies its records into partition order with
-// meta = (tile-order index) << 12 | (count - 1).
+// (count - 1).  The block then copies its records into partition order with
+// src = the record's place in tile order (over all dedup blocks: dedup block *
+// record capacity + index) and meta = count - 1.
 struct alignas(16) TileRec {
   unsigned long long key;  // encoded key
-  unsigned int tmin;       // first position of the key in the tile
+  unsigned int src;
   unsigned int meta;
 };
 
-// One distinct key of the call, indexed by its key index: the tile-order
-// position (in the record lists) of the key's first record.
-struct alignas(32) KeyInfo {
-  long long row;  // Blocks row (-1: not found / could not be inserted)
-  long long key;  // the key
-  int count;      // occurrences
+// Result of a record, at its place in tile order.  A key's index is the place
+// of its first record (the one holding its first position).
+//   first record of a key: x = occurrences, v = Blocks row (-1: not found);
+//     ids partition: x = the key index, v = the key
+//   another record: x = the key index (v is not set)
+//   y = occurrences of the key before the record's | kRecFirst
+struct alignas(16) RecRes {
+  int x;
+  unsigned int y;
+  long long v;
+};
+
+// One distinct key of the call, at its key index (written by the compaction).
+struct alignas(16) KeyInfo {
+  long long row;  // Blocks row (-1: could not be inserted)
   int uid;        // unique id (first-occurrence order)
   int start;      // first position of the key's segment of the occurrence list
-  int long_idx;   // hot-key index, -1 if count <= kLong
 };
 
 // occ_word of a rejected (reserved) key
@@ -245,13 +254,13 @@ struct alignas(16) Unit {
 struct Work {
   uint32_t* occ_word;   // [n] dedup record index (in its block) << 12 | rank in the tile
   TileRec* trec;        // [nblk * rcap] records of the dedup tiles, per block, tile order
-  int2* recres;         // [nblk * rcap] (same memory as trec) {key index, rank base | kRecFirst} per record
+  RecRes* recres;       // [nblk * rcap] result of each record, tile order (ids partition: the memory of trec)
   int32_t* nrec;        // [nblk] records of each dedup block
   TileRec* srec;        // [nblk * rcap] the same records per block in partition order
   int32_t* pcnt;        // [nblk * P] records per (block, partition)
   int32_t* poff;        // [nblk * P] their offsets in the block's partition-ordered copy
-  int2* ptmp;           // [nblk * rcap] per partition-ordered record: (tile-order index << 12 | LDS slot), rank base
-  KeyInfo* kinfo;       // [nblk * rcap] per key index
+  int2* ptmp;           // [nblk * rcap] per partition-ordered record of a swept partition: LDS slot, rank base
+  KeyInfo* kinfo;       // [nblk * rcap] per key index (null: ids partition)
   int64_t nkeyidx;      // nblk * rcap (key indices are below it)
   int32_t* inverse;     // [n]
   int64_t* occ_row;     // [n] Blocks row of each occurrence (-1: none)
@@ -274,8 +283,7 @@ struct Work {
   FrontGeom g;
 };
 
-// The record result of a key's first record (the one holding its first
-// position) carries this bit in its rank-base word.
+// The record result of a key's first record carries this bit in y.
 constexpr uint32_t kRecFirst = 0x80000000u;
 // Record tiles: dedup block b's record slots [c * kRankTile, (c + 1) *
 // kRankTile) for c < rcap / kRankTile, in block-major order.
@@ -305,11 +313,8 @@ FrontGeom front_geom(int64_t n);
 hipError_t launch_dedup_probe(const int64_t* values, int64_t n, const TableDev& t, const Work& w, int64_t* h_live,
                               int64_t tag, hipEvent_t* ev_tile, hipEvent_t* ev_part, hipStream_t s);
 // The first two dedup passes only (tile dedup, per-partition dedup): each
-// record's key index with the key's first record flagged and, unless
-// w.kinfo is null, the key info of every distinct key (t.slots null: no
-// IDMap probe, row 0).  With w.kinfo null a key index is the first record's
-// position in the partition-ordered copies (whose entry there holds the
-// key).  n > 0.
+// record's result, the first records with their key's row (the ids
+// partition, w.kinfo null: no IDMap probe, with the key).  n > 0.
 hipError_t launch_dedup_keys(const int64_t* values, int64_t n, const TableDev& t, const Work& w, hipEvent_t* ev_tile,
                              hipEvent_t* ev_part, hipStream_t s);
 // Geometry of the ids partition's owner passes.
