@@ -119,6 +119,15 @@ __device__ inline void block_excl_scan5(const int (&v)[5], int (&ex)[5], int (&t
   __syncthreads();
 }
 
+// Slot hash of a tile's LDS table (32-bit multiplies: the 64-bit mix costs
+// several times the instructions, once per id).
+__device__ inline uint32_t lds_hash(unsigned long long e) {
+  uint32_t x = static_cast<uint32_t>(e) ^ static_cast<uint32_t>(e >> 32) * 0x9E3779B1u;
+  x = (x ^ (x >> 16)) * 0x85EBCA6Bu;
+  x = (x ^ (x >> 13)) * 0xC2B2AE35u;
+  return x >> 16;
+}
+
 __device__ inline uint32_t part_of(unsigned long long e, int logP) {
   return logP == 0 ? 0u : static_cast<uint32_t>(part_hash(e) >> (64 - logP));
 }
@@ -181,24 +190,33 @@ __global__ __launch_bounds__(NT) void k_tile_dedup(const int64_t* __restrict__ v
     __syncthreads();
     int ls[kDedupItems];
     unsigned int lr[kDedupItems];
+    // the home slots of a thread's ids are tried together, then each id that
+    // met another key probes on
+    unsigned long long was[kDedupItems];
 #pragma unroll
     for (int k = 0; k < kDedupItems; ++k) {
       const int64_t i = base + k * NT + tid;
       const unsigned long long e = static_cast<unsigned long long>(raw[k]) ^ kSign;
       ls[k] = -1;
-      lr[k] = 0;
       if (i >= n) continue;
       if (e <= kEncTomb) {
         atomicOr(err, kErrKey);
         continue;
       }
-      unsigned int h = static_cast<unsigned int>(mix64(e) >> 40) & (SLOTS - 1);
-      while (true) {  // at most TILE keys in twice as many slots: terminates
-        const unsigned long long old = atomicCAS(&lkey[h], kEncEmpty, e);
-        if (old == kEncEmpty || old == e) break;
+      ls[k] = static_cast<int>(lds_hash(e) & (SLOTS - 1));
+      was[k] = atomicCAS(&lkey[ls[k]], kEncEmpty, e);
+    }
+#pragma unroll
+    for (int k = 0; k < kDedupItems; ++k) {
+      lr[k] = 0;
+      if (ls[k] < 0) continue;
+      const unsigned long long e = static_cast<unsigned long long>(raw[k]) ^ kSign;
+      unsigned int h = static_cast<unsigned int>(ls[k]);
+      while (was[k] != kEncEmpty && was[k] != e) {  // at most TILE keys in twice as many slots: terminates
         h = (h + 1) & (SLOTS - 1);
+        was[k] = atomicCAS(&lkey[h], kEncEmpty, e);
       }
-      atomicMin(&lmin[h], static_cast<unsigned int>(i));
+      atomicMin(&lmin[h], static_cast<unsigned int>(base + k * NT + tid));
       lr[k] = atomicAdd(&lcnt[h], 1u);
       ls[k] = static_cast<int>(h);
     }
@@ -240,8 +258,9 @@ __global__ __launch_bounds__(NT) void k_tile_dedup(const int64_t* __restrict__ v
     for (int q = tid; q < d; q += NT) {
       const int sl = ldense[q];
       const unsigned long long e = lkey[sl];
-      const unsigned int pr = atomicAdd(&lpc[part_of(e, g.logP)], 1u);
-      rec[nrec + q] = TileRec{e, 0u, (pr << 12) | (lcnt[sl] - 1u)};
+      const unsigned int part = part_of(e, g.logP);
+      const unsigned int pr = atomicAdd(&lpc[part], 1u);
+      rec[nrec + q] = TileRec{e, part, (pr << 12) | (lcnt[sl] - 1u)};
       lmin[sl] = nrec + static_cast<unsigned int>(q);
     }
     __syncthreads();
@@ -312,7 +331,7 @@ __global__ __launch_bounds__(NT) void k_tile_dedup(const int64_t* __restrict__ v
       for (int u = 0; u < U8; ++u) {
         const unsigned int j = j0 + u * NT;
         if (j >= nrec) continue;
-        const unsigned int o = lpc[part_of(r[u].key, g.logP)] + (r[u].meta >> 12);
+        const unsigned int o = lpc[r[u].src] + (r[u].meta >> 12);
         const TileRec x{r[u].key, src0 + j, r[u].meta & 0xFFFu};
         if (!staged) srt[o] = x;
         else if (o >= o0 && o < o1) lbuf[o - o0] = x;

@@ -207,8 +207,8 @@ struct FrontGeom {
 // in the order of the keys' first positions in the tile (so a block's
 // records, tile after tile, are in first-position order), with meta = (rank
 // of the record among its block's records of the same partition) << 12 |
-// (count - 1).  The block then copies its records into partition order with
-// src = the record's place in tile order (over all dedup blocks: dedup block *
+// (count - 1) and src = the partition.  The block then copies its records into
+// partition order with src = the record's place in tile order (over all dedup blocks: dedup block *
 // record capacity + index) and meta = count - 1.
 struct alignas(16) TileRec {
   unsigned long long key;  // encoded key
