@@ -431,7 +431,12 @@ __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w,
   __shared__ int ovf;
   const FrontGeom g = w.g;
   const int tid = threadIdx.x;
-  const int p = blockIdx.x;
+  // XCD-contiguous: block b runs on XCD b % 8, which takes the (b % 8)-th
+  // eighth of the partitions in order, so the lines that adjacent partitions
+  // share (runs of a few records per dedup block, and the count columns) are
+  // fetched into one L2 (9M ids 79 -> 70 us, 16.4M 332 -> 325, 10.6M 134 -> 131)
+  const int p = g.P >= 8 ? static_cast<int>(blockIdx.x % 8) * (g.P / 8) + static_cast<int>(blockIdx.x / 8)
+                         : static_cast<int>(blockIdx.x);
   // the partition's segments (thread tid holds blocks tid*BPT ...)
   int cn[BPT];
   int loc = 0;
@@ -1136,7 +1141,8 @@ template <bool OCC>
 __global__ __launch_bounds__(kBlock) void k_occ_init(TableDev t, Work w, int64_t n, uint32_t occ_blocks,
                                                      uint32_t unit_blocks) {
   const uint32_t b = blockIdx.x;
-  if (b < occ_blocks) occ_pass<OCC>(w, n, b);
+  // the blocks of a dedup tile on one XCD: they read the same records' results
+  if (b < occ_blocks) occ_pass<OCC>(w, n, xcd_runs<kDedupTile / (kBlock * 4)>(b, occ_blocks));
   else if (b - occ_blocks < unit_blocks) write_unit(w, static_cast<int64_t>(b - occ_blocks) * kBlock + threadIdx.x);
   else init_rows(t, w, b - occ_blocks - unit_blocks, gridDim.x - occ_blocks - unit_blocks);
 }

@@ -217,6 +217,18 @@ __device__ inline void store4_nt(int32_t* p, int a, int b, int c, int d) {
   __builtin_nontemporal_store(v, reinterpret_cast<nt_u32x4*>(p));
 }
 
+// Block b of nblk in an order where the dispatcher (block b runs on XCD b % 8)
+// puts each run of G consecutive blocks on one XCD: within every 8 G blocks
+// XCD x takes the x-th run.  The blocks of a run read the same lines into one
+// L2, and the grid still sweeps the data in order.
+template <uint32_t G>
+__device__ inline uint32_t xcd_runs(uint32_t b, uint32_t nblk) {
+  const uint32_t set = b / (8 * G) * (8 * G);
+  if (set + 8 * G > nblk) return b;  // the last, partial set
+  const uint32_t q = b - set;
+  return set + (q % 8) * G + q / 8;
+}
+
 inline unsigned grid_for(int64_t work_items, int64_t per_block, int64_t cap = 1 << 20) {
   int64_t g = (work_items + per_block - 1) / per_block;
   if (g < 1) g = 1;

@@ -269,10 +269,12 @@ __global__ __launch_bounds__(kBlock) void k_owner_scatter(Work w, int64_t n, int
 // occurrence word), the record's key index, that key's slot; -1 for a
 // rejected (reserved) key.
 __global__ __launch_bounds__(kBlock) void k_ids_inverse(Work w, const int32_t* __restrict__ kslot, int64_t n) {
-  const int64_t i0 = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * 4;
+  // the blocks of a dedup tile on one XCD: they read the same records' results
+  const uint32_t blk = xcd_runs<kDedupTile / (kBlock * 4)>(blockIdx.x, gridDim.x);
+  const int64_t i0 = (static_cast<int64_t>(blk) * kBlock + threadIdx.x) * 4;
   if (i0 >= n) return;
   static_assert(kDedupTile % (kBlock * 4) == 0, "a block's ids share a dedup tile");
-  const uint32_t base = blockIdx.x / (kDedupTile / (kBlock * 4)) / static_cast<uint32_t>(w.g.R) *
+  const uint32_t base = blk / (kDedupTile / (kBlock * 4)) / static_cast<uint32_t>(w.g.R) *
                         static_cast<uint32_t>(w.g.rcap);
   uint32_t o[4];
   if (i0 + 4 <= n) {
