@@ -101,7 +101,7 @@ Layout make_layout(int64_t n, int dim) {
   return L;
 }
 
-Work make_work(void* base, const Layout& L) {
+Work make_work(void* base, const Layout& L, int dim) {
   uint8_t* b = static_cast<uint8_t*>(base);
   Work w;
   w.occ_word = reinterpret_cast<uint32_t*>(b + L.occ_word);
@@ -132,6 +132,7 @@ Work make_work(void* base, const Layout& L) {
   w.scal = reinterpret_cast<int64_t*>(b + L.scal);
   w.gpart = reinterpret_cast<float*>(b + L.gpart);
   w.ntiles = L.ntiles;
+  w.maxu = max_units(dim);
   w.g = L.g;
   return w;
 }
@@ -566,7 +567,7 @@ rs_status check_ctx(const rs_table* t, const rs_ctx* c) {
 }
 
 Work ctx_work(const rs_ctx* c) {
-  Work w = make_work(c->workspace, make_layout(c->n, c->dim));
+  Work w = make_work(c->workspace, make_layout(c->n, c->dim), c->dim);
   w.offsets = c->offsets;
   return w;
 }
@@ -810,7 +811,7 @@ rs_status ht_find_or_insert(rs_table* t, const int64_t* keys, int64_t n, int64_t
     t->iws_bytes = t->iws ? L.total : 0;
     if (!t->iws) return fail(RS_ENOMEM, "allocation of the insert workspace failed");
   }
-  const Work w = make_work(t->iws, L);
+  const Work w = make_work(t->iws, L, t->d.dim);
   t->clock += 1;  // one lookup call
   return dedup_and_insert(t, keys, n, w, false, rows_out, n_inserted_dev, s);
 }
@@ -996,7 +997,7 @@ rs_status lookup_prepare(rs_table* t, const int64_t* values, const int64_t* offs
     for (int64_t g = 0; g < bags; ++g)
       if (h[g + 1] < h[g]) return fail(RS_EINVAL, "offsets must be nondecreasing");
   }
-  const Work w = make_work(ctx->workspace, L);
+  const Work w = make_work(ctx->workspace, L, t->d.dim);
   ctx->table = nullptr;  // published only once the work has been enqueued
   ctx->priv[0] = 0;      // 1: prepared, 2: pooled
   ctx->unique = w.unique;

@@ -16,7 +16,7 @@
 //                     gradient rows are being read)
 //   k_bwd_long        a hot key: its segment is cut into units (kUnit
 //                     positions, more for the hottest keys so a key has at
-//                     most kMaxUnits units), each XCD taking a contiguous
+//                     most max_units units), each XCD taking a contiguous
 //                     eighth of them; each unit writes its partial sum row
 //                     (no atomics)
 //   k_bwd_long_finish one block per hot key sums the partial rows of its
@@ -119,29 +119,36 @@ __device__ inline float mean_scale(const Work& w, int r, uint32_t nref) {
   return 1.0f / static_cast<float>(max(len, int64_t(1)));
 }
 
-// Sum of the gradient rows of occurrence-list positions [p0, p0 + cnt),
-// cnt <= kUnit.  The lanes of the group load the positions' gradient-row
-// indices together (one round trip), share them by shuffles, and then read
-// the gradient rows kBatch at a time.
+// The gradient-row indices of occurrence-list positions [p0, p0 + cnt), cnt <=
+// kUnit, shared out over the lanes of the group (one round trip), and their
+// mean-pooling scales.
+template <int LANES, int MODE>
+struct UnitRefs {
+  static constexpr int NR = (kUnit + LANES - 1) / LANES;  // positions per lane
+  int ref[NR];
+  float sc[NR];
+  __device__ inline void load(const Work& w, uint32_t nref, int p0, int cnt, int lane) {
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const int q = k * LANES + lane;
+      ref[k] = q < cnt ? w.occ_ref[p0 + q] : -1;
+    }
+    if (MODE == 1) {
+#pragma unroll
+      for (int k = 0; k < NR; ++k) sc[k] = mean_scale(w, ref[k], nref);
+    }
+  }
+};
+
+// Sum of the gradient rows of a UnitRefs of cnt positions: the lanes share the
+// indices by shuffles and read the rows kBatch at a time.
 template <typename GT, int E, int LANES, int MODE>
-__device__ inline void sum_positions(const Work& w, const GT* __restrict__ grad, uint32_t nref, int p0, int cnt,
-                                     int lane, float (&acc)[E]) {
+__device__ inline void sum_positions(const UnitRefs<LANES, MODE>& u, const GT* __restrict__ grad, uint32_t nref,
+                                     int cnt, int lane, float (&acc)[E]) {
   constexpr int D = LANES * E;
-  constexpr int NR = (kUnit + LANES - 1) / LANES;  // positions per lane
   // gradient rows in flight: a small batch keeps more waves resident; narrow
   // rows (<= 4 lanes) take a whole unit's rows (128 values per lane) at once
   constexpr int kBatch = LANES <= 4 ? 128 / E : 8;
-  int myref[NR];
-  float mysc[NR];
-#pragma unroll
-  for (int k = 0; k < NR; ++k) {
-    const int q = k * LANES + lane;
-    myref[k] = q < cnt ? w.occ_ref[p0 + q] : -1;
-  }
-  if (MODE == 1) {
-#pragma unroll
-    for (int k = 0; k < NR; ++k) mysc[k] = mean_scale(w, myref[k], nref);
-  }
 #pragma unroll
   for (int q0 = 0; q0 < kUnit; q0 += kBatch) {
     if (q0 >= cnt) break;
@@ -149,7 +156,7 @@ __device__ inline void sum_positions(const Work& w, const GT* __restrict__ grad,
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
       const int q = q0 + j;
-      const int r = LANES > 1 ? __shfl(myref[q / LANES], q % LANES, LANES) : myref[q];
+      const int r = LANES > 1 ? __shfl(u.ref[q / LANES], q % LANES, LANES) : u.ref[q];
       ref[j] = q < cnt && static_cast<uint32_t>(r) < nref ? r : -1;
     }
     uint4 raw[kBatch];
@@ -164,7 +171,7 @@ __device__ inline void sum_positions(const Work& w, const GT* __restrict__ grad,
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
         const int q = q0 + j;
-        const float sc = LANES > 1 ? __shfl(mysc[q / LANES], q % LANES, LANES) : mysc[q];
+        const float sc = LANES > 1 ? __shfl(u.sc[q / LANES], q % LANES, LANES) : u.sc[q];
 #pragma unroll
         for (int k = 0; k < E; ++k) x[j][k] *= sc;
       }
@@ -173,6 +180,23 @@ __device__ inline void sum_positions(const Work& w, const GT* __restrict__ grad,
     for (int j = 0; j < kBatch; ++j)
 #pragma unroll
       for (int k = 0; k < E; ++k) acc[k] += x[j][k];
+  }
+}
+
+// Sum of a unit's gradient rows, kUnit positions at a time, the next indices
+// requested before this step's rows are read.
+template <typename GT, int E, int LANES, int MODE>
+__device__ inline void sum_unit(const Work& w, const GT* __restrict__ grad, uint32_t nref, const Unit& un, int lane,
+                                float (&acc)[E]) {
+#pragma unroll
+  for (int q = 0; q < E; ++q) acc[q] = 0.f;
+  UnitRefs<LANES, MODE> cur, nxt;
+  cur.load(w, nref, un.p0, min(kUnit, un.p1 - un.p0), lane);
+  for (int p = un.p0; p < un.p1; p += kUnit) {
+    const int q = p + kUnit;
+    if (q < un.p1) nxt.load(w, nref, q, min(kUnit, un.p1 - q), lane);
+    sum_positions<GT, E, LANES, MODE>(cur, grad, nref, min(kUnit, un.p1 - p), lane, acc);
+    cur = nxt;
   }
 }
 
@@ -319,12 +343,8 @@ __device__ inline void bwd_units(const Work& w, uint32_t nref, const GT* __restr
   const int grp = threadIdx.x / LANES;
   const int64_t units = w.scal[kCNUnits];
   for (int64_t unit = blk * GPB + grp; unit < units; unit += nblk * GPB) {
-    const Unit un = w.units[unit];
     float acc[E];
-#pragma unroll
-    for (int q = 0; q < E; ++q) acc[q] = 0.f;
-    for (int p = un.p0; p < un.p1; p += kUnit)
-      sum_positions<GT, E, LANES, MODE>(w, grad, nref, p, min(kUnit, un.p1 - p), lane, acc);
+    sum_unit<GT, E, LANES, MODE>(w, grad, nref, w.units[unit], lane, acc);
     store_vals<float, E>(w.gpart + unit * D + lane * E, acc);
   }
 }
@@ -393,7 +413,7 @@ __device__ inline void finish_key(const TableDev& t, const Work& w, int64_t li, 
   const int grp = threadIdx.x / LANES;
   const int u = w.long_u[li];
   const Seg sg = w.useg[u];
-  const int nu = unit_count(sg.count);
+  const int nu = unit_count(sg.count, w.maxu);
   const int64_t u0 = w.long_start[li];
   RowFrag<WT, E> fr;
   uint8_t* rp = nullptr;
@@ -404,6 +424,8 @@ __device__ inline void finish_key(const TableDev& t, const Work& w, int64_t li, 
   float acc[E];
 #pragma unroll
   for (int q = 0; q < E; ++q) acc[q] = 0.f;
+  // two partial rows in flight (four or eight cost registers and waves: 66 ->
+  // 81 us where most hot keys have few units)
   for (int j = grp; j < nu; j += 2 * GPB) {
     float x[E], y[E];
     const float* const px = w.gpart + (u0 + j) * D + lane * E;
@@ -481,12 +503,9 @@ __global__ __launch_bounds__(kBlock) void k_bwd_small(TableDev t, Work w, uint32
   if (threadIdx.x < LANES) {
     const int lane = threadIdx.x;
     float acc[E];
-#pragma unroll
-    for (int q = 0; q < E; ++q) acc[q] = 0.f;
-    for (int p = un.p0; p < un.p1; p += kUnit)
-      sum_positions<GT, E, LANES, MODE>(w, grad, nref, p, min(kUnit, un.p1 - p), lane, acc);
+    sum_unit<GT, E, LANES, MODE>(w, grad, nref, un, lane, acc);
     store_agent<E>(w.gpart + unit * D + lane * E, acc);
-    const int nu = unit_count(w.useg[w.long_u[un.li]].count);
+    const int nu = unit_count(w.useg[w.long_u[un.li]].count, w.maxu);
     __builtin_amdgcn_s_waitcnt(0);  // the partial row (one wave's) is complete
     if (lane == 0) {
       const bool last = atomicAdd(&w.id_ref[un.li], 1) == nu - 1;
