@@ -186,23 +186,26 @@ __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64
   while (q < nb) flush();  // the last bag and any empty bags after it
 }
 
-// Padded copy: block = (bag, TCH positions); a lane group copies TCH / groups
-// positions, with their loads issued together.
-template <typename WT, int LANES, bool SMALL>
+// Padded copy: block = (bag, K positions per lane group), a lane group's loads
+// issued together, the output streamed out (nothing in the step reads it; with
+// plain stores the 402 MB of 1536 bags of 1024 slots of dim 128 bf16 took 130
+// us here, now 112, and the backward after it 70 + 69 us, now 58 + 57, for the
+// lines it had to write back), mask and gradient rows in whole lines.
+template <typename WT, int LANES, int K, bool SMALL>
 __global__ __launch_bounds__(kBlock) void k_pool_none(TableDev t, Work w, const int64_t* __restrict__ offsets,
                                                       int64_t n, int64_t bags, int64_t L, bool tail,
                                                       WT* __restrict__ out, uint8_t* __restrict__ mask) {
   constexpr int E = 16 / static_cast<int>(sizeof(WT));
   constexpr int D = LANES * E;
   constexpr int GPB = kBlock / LANES;
-  constexpr int TCH = GPB > 64 ? GPB : 64;  // positions per block
-  constexpr int K = TCH / GPB;               // positions per lane group
+  constexpr int TCH = GPB * K;  // positions per block
   const int lane = threadIdx.x % LANES;
   const int grp = threadIdx.x / LANES;
   if (blockIdx.x == 0 && threadIdx.x == 0) record_pooled_range(w, offsets, n, bags);
-  const int64_t nch = (L + TCH - 1) / TCH;
-  for (int64_t blk = blockIdx.x; blk < bags * nch; blk += gridDim.x) {
-    const int64_t g = blk / nch, c = blk % nch;
+  const uint32_t nch = static_cast<uint32_t>((L + TCH - 1) / TCH);  // bags * L < 2^31
+  const uint32_t nblk = static_cast<uint32_t>(bags) * nch;
+  for (uint32_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+    const int64_t g = blk / nch, c = blk - static_cast<uint32_t>(g) * nch;
     const int64_t b = min(max(offsets[g], int64_t(0)), n);
     const int64_t len = min(max(offsets[g + 1], b), n) - b;
     // the copied window: ids [skip, skip + min(len, L)) of the bag
@@ -222,13 +225,16 @@ __global__ __launch_bounds__(kBlock) void k_pool_none(TableDev t, Work w, const 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       if (tp[k] >= L) continue;
-      *reinterpret_cast<uint4*>(out + (g * L + tp[k]) * D + lane * E) = v[k];
-      if (lane == 0) {
-        mask[g * L + tp[k]] = tp[k] < len ? 1 : 0;
-        if (tp[k] < len)
-          write_ref<SMALL>(w, b + skip + tp[k], SMALL ? w.occ_pos[b + skip + tp[k]] : 0,
-                           static_cast<int>(g * L + tp[k]));
-      }
+      const nt_u32x4 x = {v[k].x, v[k].y, v[k].z, v[k].w};
+      __builtin_nontemporal_store(x, reinterpret_cast<nt_u32x4*>(out + (g * L + tp[k]) * D + lane * E));
+    }
+    // the mask and the ids' gradient rows: consecutive threads, consecutive positions
+    for (int q = threadIdx.x; q < TCH; q += kBlock) {
+      const int64_t tq = c * TCH + q;
+      if (tq >= L) break;
+      mask[g * L + tq] = tq < len ? 1 : 0;
+      if (tq < len)
+        write_ref<SMALL>(w, b + skip + tq, SMALL ? w.occ_pos[b + skip + tq] : 0, static_cast<int>(g * L + tq));
     }
     if (c == 0 && lane == 0) {
       // ids outside the window (past L, or before skip): in the occurrence
@@ -240,6 +246,15 @@ __global__ __launch_bounds__(kBlock) void k_pool_none(TableDev t, Work w, const 
   }
 }
 
+template <typename WT, int LANES, int K, bool SMALL>
+static void pool_none_launch(const TableDev& t, const Work& w, const int64_t* offsets, int64_t n, int64_t bags,
+                             bool tail, int64_t L, void* out, uint8_t* mask, hipEvent_t e0, hipEvent_t e1,
+                             hipStream_t s) {
+  constexpr int TCH = kBlock / LANES * K;
+  hipExtLaunchKernelGGL((k_pool_none<WT, LANES, K, SMALL>), dim3(grid_for(bags * ((L + TCH - 1) / TCH), 1, 1 << 20)),
+                        dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n, bags, L, tail, static_cast<WT*>(out), mask);
+}
+
 // The launch takes optional start / stop events that the dispatch itself
 // timestamps (the kernel's own execution, no extra packets on the stream).
 template <typename WT, int LANES, bool SMALL>
@@ -248,10 +263,12 @@ static hipError_t pool_mode(const TableDev& t, const Work& w, const int64_t* off
                             hipStream_t s) {
   constexpr int GPB = kBlock / LANES;
   if (mode == 2 || mode == 3) {
-    constexpr int TCH = GPB > 64 ? GPB : 64;
-    const int64_t nch = (pad_len + TCH - 1) / TCH;
-    hipExtLaunchKernelGGL((k_pool_none<WT, LANES, SMALL>), dim3(grid_for(bags * nch, 1, 1 << 20)), dim3(kBlock), 0, s,
-                          e0, e1, 0, t, w, offsets, n, bags, pad_len, mode == 3, static_cast<WT*>(out), mask);
+    // positions per lane group: as many as the pad length fills, up to 8
+    const bool tail = mode == 3;
+    if (pad_len > 4 * GPB) pool_none_launch<WT, LANES, 8, SMALL>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
+    else if (pad_len > 2 * GPB) pool_none_launch<WT, LANES, 4, SMALL>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
+    else if (pad_len > GPB) pool_none_launch<WT, LANES, 2, SMALL>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
+    else pool_none_launch<WT, LANES, 1, SMALL>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
   } else {
     // one lane group per `per` bags (one bag per lane), 16 rows in flight
     float* o = static_cast<float*>(out);
