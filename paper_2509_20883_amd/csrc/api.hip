@@ -527,7 +527,7 @@ rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const 
   }
   RS_HIP(launch_compact_insert(values, n, t->dev(), w, occ_lists, t->ev(RS_K_COMPACT_INSERT),
                                t->ev(RS_K_INIT_ROWS), t->ev(RS_K_OCC), s));
-  if (occ_lists && small_batch(n)) RS_HIP(launch_clear_refs(w, n, s));
+  if (occ_lists && small_batch(n)) RS_HIP(launch_clear_counts(w, n, s));
   if (!occ_lists) RS_HIP(launch_map_rows(w, n, rows_out, n_inserted, s));
   return RS_OK;
 }

@@ -1109,7 +1109,12 @@ __device__ inline void occ_pass(const Work& w, int64_t n, uint32_t blk) {
     if (OCC) {
       *reinterpret_cast<longlong2*>(w.occ_row + i0) = make_longlong2(a[0].row, a[1].row);
       *reinterpret_cast<longlong2*>(w.occ_row + i0 + 2) = make_longlong2(a[2].row, a[3].row);
-      store4_nt(w.occ_pos + i0, pos[0], pos[1], pos[2], pos[3]);
+      if (list_in_pool(n)) {  // the pool reads the positions next, and fills the list: no gradient row yet
+        *reinterpret_cast<int4*>(w.occ_pos + i0) = make_int4(pos[0], pos[1], pos[2], pos[3]);
+        *reinterpret_cast<int4*>(w.occ_ref + i0) = make_int4(-1, -1, -1, -1);
+      } else {
+        store4_nt(w.occ_pos + i0, pos[0], pos[1], pos[2], pos[3]);
+      }
     }
   } else {
     for (int k = 0; k < 4 && i0 + k < n; ++k) {
@@ -1117,6 +1122,7 @@ __device__ inline void occ_pass(const Work& w, int64_t n, uint32_t blk) {
       if (OCC) {
         w.occ_row[i0 + k] = a[k].row;
         w.occ_pos[i0 + k] = pos[k];
+        if (list_in_pool(n)) w.occ_ref[i0 + k] = -1;
       }
     }
   }
@@ -1456,16 +1462,14 @@ __global__ __launch_bounds__(kSmallNT) void k_small_rows(const int64_t* __restri
   if (blockIdx.x == 0 && tid == 0) publish_live(h_live, tag, res.published);  // last: a store to host memory
 }
 
-__global__ __launch_bounds__(kBlock) void k_clear_refs(Work w, int n) {
+__global__ __launch_bounds__(kBlock) void k_clear_counts(Work w, int n) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  w.occ_ref[i] = -1;
-  w.id_ref[i] = 0;
+  if (i < n) w.id_ref[i] = 0;
 }
 
-hipError_t launch_clear_refs(const Work& w, int64_t n, hipStream_t s) {
+hipError_t launch_clear_counts(const Work& w, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  k_clear_refs<<<grid_for(n, kBlock), kBlock, 0, s>>>(w, static_cast<int>(n));
+  k_clear_counts<<<grid_for(n, kBlock), kBlock, 0, s>>>(w, static_cast<int>(n));
   return hipGetLastError();
 }
 

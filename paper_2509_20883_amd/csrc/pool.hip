@@ -7,8 +7,8 @@
 // occurrence its row (occ_row); these kernels read each occurrence's row
 // with 16-byte vector loads, one lane group of D*sizeof(row)/16 lanes per
 // row, and write the gradient row of each id (id_ref, in id order), from
-// which the backward builds its occurrence list (a small batch's list is
-// written here).
+// which the backward builds its occurrence list (up to kPoolList ids
+// the list is written here).
 //
 // A lane group handles one bag per lane and requests 16 rows of them at a
 // time, for single-id and long bags alike.
@@ -30,11 +30,11 @@ __device__ inline void record_pooled_range(const Work& w, const int64_t* offsets
 }
 
 // Gradient row of id i: kept in id order for the backward's list launch, or,
-// for a small batch, put at the id's place in the occurrence list at once
+// up to kPoolList ids, put at the id's place in the occurrence list at once
 // (pos: occ_pos[i], -1 for an id that takes no part).
-template <bool SMALL>
+template <bool LIST>
 __device__ inline void write_ref(const Work& w, int64_t i, int pos, int ref) {
-  if (!SMALL) w.id_ref[i] = ref;
+  if (!LIST) w.id_ref[i] = ref;
   else if (pos >= 0) w.occ_ref[pos] = ref;
 }
 
@@ -89,7 +89,7 @@ __device__ inline int64_t group_incl_scan(int64_t v, int lane) {
 // the list written on the way).
 constexpr int64_t kPoolBlocks = 1024;
 
-template <typename WT, int LANES, int MODE, int C, bool SMALL>
+template <typename WT, int LANES, int MODE, int C, bool LIST>
 __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64_t* __restrict__ offsets, int64_t n,
                                                  int64_t bags, int per, float* __restrict__ out) {
   constexpr int E = 16 / static_cast<int>(sizeof(WT));
@@ -159,8 +159,8 @@ __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64
       if (r >= 0) x[c] = *reinterpret_cast<const uint4*>(t.store.row(r) + lane * 16);
     }
     if (t0 + C < total) load_idx(t0 + C);  // the next chunk's row ids replace rr
-    int lp[J];  // small batch: list positions of this lane's ids of the chunk
-    if (SMALL) {
+    int lp[J];  // list positions of this lane's ids of the chunk
+    if (LIST) {
 #pragma unroll
       for (int j = 0; j < J; ++j) lp[j] = w.occ_pos[min(p0 + t0 + min(lane + j * LANES, C - 1), n32 - 1)];
     }
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64
     for (int j = 0; j < J; ++j) {
       const int c = lane + j * LANES;
       if (c >= C || t0 + c >= total || p0 + t0 + c >= n32) continue;
-      write_ref<SMALL>(w, p0 + t0 + c, SMALL ? lp[j] : 0, static_cast<int>(g0 + myq[j]));
+      write_ref<LIST>(w, p0 + t0 + c, LIST ? lp[j] : 0, static_cast<int>(g0 + myq[j]));
     }
   }
   while (q < nb) flush();  // the last bag and any empty bags after it
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kBlock) void k_pool(TableDev t, Work w, const int64
 // plain stores the 402 MB of 1536 bags of 1024 slots of dim 128 bf16 took 130
 // us here, now 112, and the backward after it 70 + 69 us, now 58 + 57, for the
 // lines it had to write back), mask and gradient rows in whole lines.
-template <typename WT, int LANES, int K, bool SMALL>
+template <typename WT, int LANES, int K, bool LIST>
 __global__ __launch_bounds__(kBlock) void k_pool_none(TableDev t, Work w, const int64_t* __restrict__ offsets,
                                                       int64_t n, int64_t bags, int64_t L, bool tail,
                                                       WT* __restrict__ out, uint8_t* __restrict__ mask) {
@@ -234,30 +234,30 @@ __global__ __launch_bounds__(kBlock) void k_pool_none(TableDev t, Work w, const 
       if (tq >= L) break;
       mask[g * L + tq] = tq < len ? 1 : 0;
       if (tq < len)
-        write_ref<SMALL>(w, b + skip + tq, SMALL ? w.occ_pos[b + skip + tq] : 0, static_cast<int>(g * L + tq));
+        write_ref<LIST>(w, b + skip + tq, LIST ? w.occ_pos[b + skip + tq] : 0, static_cast<int>(g * L + tq));
     }
     if (c == 0 && lane == 0) {
       // ids outside the window (past L, or before skip): in the occurrence
       // list (the key is touched) but without a gradient row
       const int64_t x0 = tail ? 0 : L, x1 = tail ? skip : len;
       for (int64_t tpos = x0 + grp; tpos < x1; tpos += GPB)
-        write_ref<SMALL>(w, b + tpos, SMALL ? w.occ_pos[b + tpos] : 0, -1);
+        write_ref<LIST>(w, b + tpos, LIST ? w.occ_pos[b + tpos] : 0, -1);
     }
   }
 }
 
-template <typename WT, int LANES, int K, bool SMALL>
+template <typename WT, int LANES, int K, bool LIST>
 static void pool_none_launch(const TableDev& t, const Work& w, const int64_t* offsets, int64_t n, int64_t bags,
                              bool tail, int64_t L, void* out, uint8_t* mask, hipEvent_t e0, hipEvent_t e1,
                              hipStream_t s) {
   constexpr int TCH = kBlock / LANES * K;
-  hipExtLaunchKernelGGL((k_pool_none<WT, LANES, K, SMALL>), dim3(grid_for(bags * ((L + TCH - 1) / TCH), 1, 1 << 20)),
+  hipExtLaunchKernelGGL((k_pool_none<WT, LANES, K, LIST>), dim3(grid_for(bags * ((L + TCH - 1) / TCH), 1, 1 << 20)),
                         dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n, bags, L, tail, static_cast<WT*>(out), mask);
 }
 
 // The launch takes optional start / stop events that the dispatch itself
 // timestamps (the kernel's own execution, no extra packets on the stream).
-template <typename WT, int LANES, bool SMALL>
+template <typename WT, int LANES, bool LIST>
 static hipError_t pool_mode(const TableDev& t, const Work& w, const int64_t* offsets, int64_t n, int64_t bags,
                             int mode, int64_t pad_len, void* out, uint8_t* mask, hipEvent_t e0, hipEvent_t e1,
                             hipStream_t s) {
@@ -265,10 +265,10 @@ static hipError_t pool_mode(const TableDev& t, const Work& w, const int64_t* off
   if (mode == 2 || mode == 3) {
     // positions per lane group: as many as the pad length fills, up to 8
     const bool tail = mode == 3;
-    if (pad_len > 4 * GPB) pool_none_launch<WT, LANES, 8, SMALL>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
-    else if (pad_len > 2 * GPB) pool_none_launch<WT, LANES, 4, SMALL>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
-    else if (pad_len > GPB) pool_none_launch<WT, LANES, 2, SMALL>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
-    else pool_none_launch<WT, LANES, 1, SMALL>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
+    if (pad_len > 4 * GPB) pool_none_launch<WT, LANES, 8, LIST>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
+    else if (pad_len > 2 * GPB) pool_none_launch<WT, LANES, 4, LIST>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
+    else if (pad_len > GPB) pool_none_launch<WT, LANES, 2, LIST>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
+    else pool_none_launch<WT, LANES, 1, LIST>(t, w, offsets, n, bags, tail, pad_len, out, mask, e0, e1, s);
   } else {
     // one lane group per `per` bags (one bag per lane), 16 rows in flight
     float* o = static_cast<float*>(out);
@@ -276,27 +276,27 @@ static hipError_t pool_mode(const TableDev& t, const Work& w, const int64_t* off
     while (per > 1 && (bags + per * GPB - 1) / (per * GPB) < kPoolBlocks) per >>= 1;
     const unsigned g = grid_for(bags, static_cast<int64_t>(GPB) * per, int64_t(1) << 31);
     if (mode == 1)
-      hipExtLaunchKernelGGL((k_pool<WT, LANES, 1, 16, SMALL>), dim3(g), dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n,
+      hipExtLaunchKernelGGL((k_pool<WT, LANES, 1, 16, LIST>), dim3(g), dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n,
                             bags, per, o);
     else
-      hipExtLaunchKernelGGL((k_pool<WT, LANES, 0, 16, SMALL>), dim3(g), dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n,
+      hipExtLaunchKernelGGL((k_pool<WT, LANES, 0, 16, LIST>), dim3(g), dim3(kBlock), 0, s, e0, e1, 0, t, w, offsets, n,
                             bags, per, o);
   }
   return hipGetLastError();
 }
 
-template <typename WT, bool SMALL>
+template <typename WT, bool LIST>
 static hipError_t pool_dim(const TableDev& t, const Work& w, const int64_t* offsets, int64_t n, int64_t bags, int mode,
                            int64_t pad_len, void* out, uint8_t* mask, hipEvent_t e0, hipEvent_t e1, hipStream_t s) {
   constexpr int E = 16 / static_cast<int>(sizeof(WT));
   switch (t.dim / E) {
-    case 1: return pool_mode<WT, 1, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 2: return pool_mode<WT, 2, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 4: return pool_mode<WT, 4, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 8: return pool_mode<WT, 8, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 16: return pool_mode<WT, 16, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 32: return pool_mode<WT, 32, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
-    case 64: return pool_mode<WT, 64, SMALL>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 1: return pool_mode<WT, 1, LIST>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 2: return pool_mode<WT, 2, LIST>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 4: return pool_mode<WT, 4, LIST>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 8: return pool_mode<WT, 8, LIST>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 16: return pool_mode<WT, 16, LIST>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 32: return pool_mode<WT, 32, LIST>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
+    case 64: return pool_mode<WT, 64, LIST>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -305,7 +305,7 @@ hipError_t launch_pool(const TableDev& t, const Work& w, const int64_t* offsets,
                        int64_t pad_len, void* out, uint8_t* mask, hipEvent_t* ev, hipStream_t s) {
   if (bags <= 0) return hipSuccess;
   hipEvent_t e0 = ev ? ev[0] : nullptr, e1 = ev ? ev[1] : nullptr;
-  if (small_batch(n))
+  if (list_in_pool(n))
     return t.row_dtype ? pool_dim<uint16_t, true>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s)
                        : pool_dim<float, true>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
   return t.row_dtype ? pool_dim<uint16_t, false>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s)
