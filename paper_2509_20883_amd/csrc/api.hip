@@ -242,7 +242,7 @@ struct rs_table {
   int64_t* free_rows = nullptr;
   int64_t free_cap = 0;
   // host view of the live count: an upper bound.  Every insert call gets a
-  // 16-bit tag; its scan kernel stores (tag << 48) | exact live count into
+  // 16-bit tag; its compaction kernel stores (tag << 48) | exact live count into
   // h_pin[0], and bound_after[tag % kTags] remembers the host's bound right
   // after that call was enqueued, so a published count refreshes the bound
   // by the calls enqueued since (bound_after[.] = -1: no refresh from it).
@@ -437,7 +437,7 @@ rs_status grow_for(rs_table* t, int64_t keys_need, int64_t tombs, int64_t rows_n
   return provision_rows(t, std::min(rows_need, t->limit), s);
 }
 
-// Lower the host's bound on live rows with the newest count a scan kernel
+// Lower the host's bound on live rows with the newest count a compaction kernel
 // has published (calls enqueued after it keep their share of the bound).
 void refresh_bound(rs_table* t) {
   const int64_t v = __atomic_load_n(t->h_pin, __ATOMIC_ACQUIRE);
@@ -473,7 +473,7 @@ void record_pair(hipEvent_t* ev, hipStream_t s) {
 rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const Work& w, bool occ_lists,
                            int64_t* rows_out, int64_t* n_inserted, hipStream_t s) {
   rs_status st = RS_OK;
-  const int64_t tag = next_tag(t);
+  int64_t tag = next_tag(t);
   if (n > 0 && small_batch(n)) {
     // its front end reserves rows and inserts in one go: only where n new keys
     // are known to fit
@@ -488,7 +488,7 @@ rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const 
       return RS_OK;
     }
   }
-  RS_HIP(launch_dedup_probe(values, n, t->dev(), w, t->h_pin, tag, t->ev(RS_K_TILE_DEDUP), t->ev(RS_K_PARTITION), s));
+  RS_HIP(launch_dedup_probe(values, n, t->dev(), w, t->ev(RS_K_TILE_DEDUP), t->ev(RS_K_PARTITION), s));
   refresh_bound(t);
   const int64_t bound = t->live_bound + n;
   if (bound > t->limit || bound > t->rows_prov) {
@@ -515,17 +515,16 @@ rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const 
     }
     int64_t tombs = 0;
     RS_HIP(hipMemcpy(&tombs, t->d_scal + kTTomb, sizeof(int64_t), hipMemcpyDeviceToHost));
-    // redo the reservation against the grown table (published under a new
-    // tag: the scan's count may predate the growth)
+    // redo the reservation against the grown table
     reset_bound(t, std::max(keys_need + tombs, rows_need));
-    const int64_t tag2 = next_tag(t);
-    RS_HIP(launch_rereserve(w, t->dev(), t->h_pin, tag2, s));
-    t->bound_after[tag2 % rs_table::kTags] = t->live_bound;
+    tag = next_tag(t);
+    RS_HIP(launch_rereserve(w, t->dev(), s));
+    t->bound_after[tag % rs_table::kTags] = t->live_bound;
   } else {
     t->live_bound = bound;
     t->bound_after[tag % rs_table::kTags] = t->live_bound;
   }
-  RS_HIP(launch_compact_insert(values, n, t->dev(), w, occ_lists, t->ev(RS_K_COMPACT_INSERT),
+  RS_HIP(launch_compact_insert(values, n, t->dev(), w, occ_lists, t->h_pin, tag, t->ev(RS_K_COMPACT_INSERT),
                                t->ev(RS_K_INIT_ROWS), t->ev(RS_K_OCC), s));
   if (occ_lists && small_batch(n)) RS_HIP(launch_clear_counts(w, n, s));
   if (!occ_lists) RS_HIP(launch_map_rows(w, n, rows_out, n_inserted, s));

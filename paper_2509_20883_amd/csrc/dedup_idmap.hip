@@ -770,14 +770,6 @@ __device__ inline void store_reservation(int64_t* cscal, int64_t* tscal, int64_t
   tscal[kTFree] = r.ftop - r.take;
 }
 
-__device__ inline void reserve_and_publish(int64_t* cscal, int64_t* tscal, int64_t req, int64_t hw, int64_t keys,
-                                           int64_t F, int64_t* h_live, int64_t tag) {
-  const int64_t tcap[3] = {tscal[kTLimit], tscal[kTRowCap], tscal[kTTomb]};
-  const Reservation r = reservation(req, hw, keys, F, tcap);
-  store_reservation(cscal, tscal, req, keys, r);
-  publish_live(h_live, tag, r.published);
-}
-
 // Scan of the five tile-sum arrays: block c scans chunk c (kScanChunk tiles,
 // R per thread) in place and stores the chunk's totals; the last block to
 // finish (a counter, no waiting) scans the chunk totals in place, reserves
@@ -786,12 +778,15 @@ __device__ inline void reserve_and_publish(int64_t* cscal, int64_t* tscal, int64
 template <int R>
 __global__ __launch_bounds__(1024) void k_scan5(int32_t* __restrict__ bsum, int64_t nb, int64_t ntiles,
                                                 int32_t* __restrict__ csum, int64_t nch, int64_t* cscal,
-                                                int64_t* tscal, int64_t* h_live, int64_t tag) {
+                                                int64_t* tscal) {
   static_assert(1024 * R == kScanChunk, "one chunk per block");
   __shared__ int sh[1024 / kWave + 1][5];
   __shared__ bool last;
   const int64_t c = blockIdx.x;
   const int64_t lo = c * kScanChunk + static_cast<int64_t>(threadIdx.x) * R;
+  int64_t ts[6];  // the table's scalars, read ahead of the scan (the last block's first thread uses them)
+#pragma unroll
+  for (int q = 0; q < 6; ++q) ts[q] = tscal[q == 5 ? kTTomb : q == 4 ? kTFree : q == 3 ? kTKeys : q == 2 ? kTRowCap : q];
   int v[5][R];
 #pragma unroll
   for (int a = 0; a < 5; ++a)
@@ -861,19 +856,22 @@ __global__ __launch_bounds__(1024) void k_scan5(int32_t* __restrict__ bsum, int6
   cscal[kCNewReq] = tot[2];
   cscal[kCNLong] = tot[3];
   cscal[kCNUnits] = tot[4];
-  reserve_and_publish(cscal, tscal, tot[2], tscal[kTLive], tscal[kTKeys], tscal[kTFree], h_live, tag);
+  const int64_t tcap[3] = {ts[1], ts[2], ts[5]};
+  const Reservation r = reservation(tot[2], ts[0], ts[3], ts[4], tcap);
+  store_reservation(cscal, tscal, tot[2], ts[3], r);
 }
 
 // After the host grew the table: reserve again from the same counts.
-__global__ void k_rereserve(int64_t* cscal, int64_t* tscal, int64_t* h_live, int64_t tag) {
-  reserve_and_publish(cscal, tscal, cscal[kCNewReq], cscal[kCBaseLive], cscal[kCBaseKeys], cscal[kCFreeTop], h_live,
-                      tag);
+__global__ void k_rereserve(int64_t* cscal, int64_t* tscal) {
+  const int64_t tcap[3] = {tscal[kTLimit], tscal[kTRowCap], tscal[kTTomb]};
+  const Reservation r = reservation(cscal[kCNewReq], cscal[kCBaseLive], cscal[kCBaseKeys], cscal[kCFreeTop], tcap);
+  store_reservation(cscal, tscal, cscal[kCNewReq], cscal[kCBaseKeys], r);
 }
 
 __global__ void k_zero_scalars(int64_t* cscal) { cscal[threadIdx.x] = 0; }
 
-hipError_t launch_rereserve(const Work& w, const TableDev& t, int64_t* h_live, int64_t tag, hipStream_t s) {
-  k_rereserve<<<1, 1, 0, s>>>(w.scal, t.scal, h_live, tag);
+hipError_t launch_rereserve(const Work& w, const TableDev& t, hipStream_t s) {
+  k_rereserve<<<1, 1, 0, s>>>(w.scal, t.scal);
   return hipGetLastError();
 }
 
@@ -908,8 +906,8 @@ hipError_t launch_dedup_keys(const int64_t* values, int64_t n, const TableDev& t
   return hipGetLastError();
 }
 
-hipError_t launch_dedup_probe(const int64_t* values, int64_t n, const TableDev& t, const Work& w, int64_t* h_live,
-                              int64_t tag, hipEvent_t* ev_tile, hipEvent_t* ev_part, hipStream_t s) {
+hipError_t launch_dedup_probe(const int64_t* values, int64_t n, const TableDev& t, const Work& w, hipEvent_t* ev_tile,
+                              hipEvent_t* ev_part, hipStream_t s) {
   if (n <= 0) {
     k_zero_scalars<<<1, kCScalars, 0, s>>>(w.scal);
     return hipGetLastError();
@@ -920,7 +918,7 @@ hipError_t launch_dedup_probe(const int64_t* values, int64_t n, const TableDev& 
   k_first_sums<kBlock><<<static_cast<unsigned>(nb), kBlock, 0, s>>>(w);
   const int64_t nch = (nb + kScanChunk - 1) / kScanChunk;
   k_scan5<kScanChunk / 1024><<<static_cast<unsigned>(nch), 1024, 0, s>>>(w.bsum, nb, w.ntiles, w.csum, nch, w.scal,
-                                                                          t.scal, h_live, tag);
+                                                                          t.scal);
   if (ev_part && ev_part[1]) (void)hipEventRecord(ev_part[1], s);
   return hipGetLastError();
 }
@@ -930,10 +928,15 @@ hipError_t launch_dedup_probe(const int64_t* values, int64_t n, const TableDev& 
 // ---------------------------------------------------------------------------
 
 template <int NT>
-__global__ __launch_bounds__(NT) void k_compact(TableDev t, Work w) {
+__global__ __launch_bounds__(NT) void k_compact(TableDev t, Work w, int64_t* h_live, int64_t tag) {
   __shared__ int sh[NT / kWave + 1][5];
   const int b = blockIdx.x;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && w.scal[kCTrunc]) atomicOr(reinterpret_cast<int*>(&t.scal[kTErr]), kErrFull);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (w.scal[kCTrunc]) atomicOr(reinterpret_cast<int*>(&t.scal[kTErr]), kErrFull);
+    // the host's bound on the live count, published here and not at the end of
+    // the scan: a store to host memory that no launch waits for behind it
+    publish_live(h_live, tag, max(t.scal[kTKeys] + t.scal[kTTomb], t.scal[kTLive]));
+  }
   const RecTile x = rec_tile(w, b);
   if (empty_tile(x)) return;  // block-uniform: no keys, nothing to write
   int pre[5];  // the record tile's exclusive prefixes (keys, count, new, hot, units)
@@ -1157,11 +1160,11 @@ __global__ __launch_bounds__(kBlock) void k_occ_init(TableDev t, Work w, int64_t
 }
 
 hipError_t launch_compact_insert(const int64_t* values, int64_t n, const TableDev& t, const Work& w, bool occ_lists,
-                                 hipEvent_t* ev_compact, hipEvent_t* ev_init, hipEvent_t* ev_occ, hipStream_t s) {
+                                 int64_t* h_live, int64_t tag, hipEvent_t* ev_compact, hipEvent_t* ev_init, hipEvent_t* ev_occ, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int64_t nb = record_tiles(w.g);
   if (ev_compact && ev_compact[0]) (void)hipEventRecord(ev_compact[0], s);
-  k_compact<kBlock><<<static_cast<unsigned>(nb), kBlock, 0, s>>>(t, w);
+  k_compact<kBlock><<<static_cast<unsigned>(nb), kBlock, 0, s>>>(t, w, h_live, tag);
   if (ev_compact && ev_compact[1]) (void)hipEventRecord(ev_compact[1], s);
   // one launch: the per-occurrence pass and the new rows (the init-rows and
   // occurrence events both bracket it)

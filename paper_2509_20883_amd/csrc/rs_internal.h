@@ -317,11 +317,9 @@ FrontGeom front_geom(int64_t n);
 // Dedup of the call's keys in first-occurrence order and the IDMap probe
 // (ends before the insert): tile dedup, partition-count scan, scatter into
 // partitions, per-partition dedup + probe, tile sums of the first
-// occurrences and their scan.  The scan also stores (tag << 48) | (live rows
-// after the call) to h_live (pinned host memory; may be null), so the host
-// can refresh its bound on the live count without a copy or an event.
-hipError_t launch_dedup_probe(const int64_t* values, int64_t n, const TableDev& t, const Work& w, int64_t* h_live,
-                              int64_t tag, hipEvent_t* ev_tile, hipEvent_t* ev_part, hipStream_t s);
+// occurrences and their scan.
+hipError_t launch_dedup_probe(const int64_t* values, int64_t n, const TableDev& t, const Work& w, hipEvent_t* ev_tile,
+                              hipEvent_t* ev_part, hipStream_t s);
 // The first two dedup passes only (tile dedup, per-partition dedup): each
 // record's result, the first records with their key's row (the ids
 // partition, w.kinfo null: no IDMap probe, with the key).  n > 0.
@@ -340,12 +338,14 @@ hipError_t launch_ids_partition(const int64_t* values, int64_t n, int G, uint64_
                                 int64_t* keys_out, int64_t* shard_offsets, int64_t* info, hipStream_t s);
 // unique / segments / rows / IDMap insert / row init, then the per-occurrence
 // pass: inverse[] and, for a forward (occ_lists), each occurrence's row and
-// list position and the hot keys' backward units
+// list position and the hot keys' backward units.  Also stores (tag << 48) |
+// (live rows after the call) to h_live (pinned host memory; may be null), so
+// the host can refresh its bound on the live count without a copy or an event.
 hipError_t launch_compact_insert(const int64_t* values, int64_t n, const TableDev& t, const Work& w, bool occ_lists,
-                                 hipEvent_t* ev_compact, hipEvent_t* ev_init, hipEvent_t* ev_occ, hipStream_t s);
+                                 int64_t* h_live, int64_t tag, hipEvent_t* ev_compact, hipEvent_t* ev_init, hipEvent_t* ev_occ, hipStream_t s);
 // A small batch (0 < n <= kSmallIds) on a table with room for n new keys: the
 // whole front end up to and including the new rows (publishes the live count
-// as launch_dedup_probe).  occ_lists: a forward; else rows_out [n] and
+// as launch_compact_insert).  occ_lists: a forward; else rows_out [n] and
 // n_inserted (may be null) receive the rows and the number inserted.
 hipError_t launch_small_front(const int64_t* values, int64_t n, const TableDev& t, const Work& w, bool occ_lists,
                               int64_t* h_live, int64_t tag, int64_t* rows_out, int64_t* n_inserted,
@@ -354,7 +354,7 @@ hipError_t launch_small_front(const int64_t* values, int64_t n, const TableDev& 
 // general front end
 hipError_t launch_clear_counts(const Work& w, int64_t n, hipStream_t s);
 // redo the row reservation of the last scan after the table has grown
-hipError_t launch_rereserve(const Work& w, const TableDev& t, int64_t* h_live, int64_t tag, hipStream_t s);
+hipError_t launch_rereserve(const Work& w, const TableDev& t, hipStream_t s);
 hipError_t launch_map_rows(const Work& w, int64_t n, int64_t* rows_out, int64_t* n_inserted, hipStream_t s);
 hipError_t launch_find(const TableDev& t, const int64_t* keys, int64_t n, int64_t* rows_out, hipStream_t s);
 hipError_t launch_pool(const TableDev& t, const Work& w, const int64_t* offsets, int64_t n, int64_t bags, int mode,
