@@ -1,0 +1,53 @@
+"""Both sides of the dispatch rules on batch size, against the oracle.
+
+The occurrence list is written by the pool up to 2^21 ids and by a launch of
+the backward above; a hot key has at most 4096 units in rows of dim <= 16 and
+1024 in wider ones (a key of 140,000 occurrences passes both limits); the ids
+partition keeps at most 2048 owner blocks (above 2^21 ids a block takes several
+record tiles) and scans up to 8192, up to 16384, or more counts.  Integers
+bit-exact, sums and updates within the step parity's bounds (tests/parity.py).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2509_20883_amd import recis as R
+from paper_2509_20883_amd import workloads as W
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _ids(n, g):
+    k = g.integers(0, 60000, size=n)
+    k[g.permutation(n)[:140000]] = 1 << 33
+    return k.astype(np.int64)
+
+
+@pytest.mark.parametrize("dim", [16, 32])
+@pytest.mark.parametrize("n", [(1 << 21) - 3, 1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("mode", [W.SUM, W.MEAN])
+def test_list_and_unit_limits(n, dim, mode):
+    print("dispatch edges", n, dim, mode, flush=True)
+    w = W.workload(0)
+    w.mode, w.dim, w.capacity_slots, w.block_rows = mode, dim, 1 << 18, 1 << 16
+    g = np.random.default_rng(n + dim)
+    gt, ot = P.gpu_table(w), P.oracle_table(w)
+    bags = n // 12
+    off = np.concatenate([[0], np.sort(g.integers(0, n + 1, size=bags - 1)), [n]]).astype(np.int64)
+    b = W.Batch(values=_ids(n, g), offsets=off, n_features=1, batch=bags)
+    P.run_step_parity(w, gt, ot, b, g.standard_normal((bags, dim)).astype(np.float32), 0)
+    gt.check()
+    gt.close()
+
+
+@pytest.mark.parametrize("n,G", [((1 << 21) - 1, 3), ((1 << 21) + 1, 4), ((1 << 21) + 1, 9), (2600001, 100),
+                                 (4200003, 7), (1 << 20, 8), ((1 << 20) + 1, 8), (1 << 20, 16), ((1 << 20) + 1, 16)])
+def test_ids_partition_owner_blocks(n, G):
+    print("owner blocks", n, G, flush=True)
+    vals = np.random.default_rng(G).integers(0, n // 3, size=n).astype(np.int64) * 0x9E3779B1
+    keys, offs, inv, info = (x.cpu().numpy() for x in R.ids_partition(torch.from_numpy(vals).cuda(), G, 7))
+    ek, eo, ei, _ = O.ids_partition(vals, G, 7)
+    assert int(info[0]) == len(ek) and np.array_equal(keys[:len(ek)], ek)
+    assert np.array_equal(offs, eo) and np.array_equal(inv, ei)

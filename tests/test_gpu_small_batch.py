@@ -1,10 +1,10 @@
-"""Batches around the one-block front end (at most 8192 ids) against the oracle.
+"""Batches around the two-launch front end (at most 8192 ids) against the oracle.
 
 Integers bit-exact, sums and updates within the step parity's bounds
 (tests/parity.py).  The first batch of a table needs Blocks, so it takes the
-general front end at a small size; the later ones find room and take the one
-block, with keys known, new, repeated and hot (hot-key units from 33
-occurrences on).  8193 ids are past the one block.
+general front end at a small size; the later ones find room and take the two
+launches, with keys known, new, repeated and hot (hot-key units from 33
+occurrences on).  8193 ids take the general front end.
 """
 import numpy as np
 import pytest
