@@ -411,6 +411,8 @@ def trace_from(a):
         by[_kname(r)].append((int(r["Dispatch_Id"]), (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
     step = {k: v for k, v in by.items() if k.startswith("rs::") and "probe" not in k and "rehash" not in k
             and "map_rows" not in k and "k_occ_init<false>" not in k and "rereserve" not in k}
+    if getattr(a, "evict_age", -1) < 0:  # a kernel of the set-up alone (the scratch table's small batch) is no part of a step
+        step = {k: v for k, v in step.items() if len(v) >= a.steps}
     how = (f"--op {a.op} --shards {a.shards or 8}" if a.op == "ids-partition" else
            f"--op {a.op}" if a.op != "step" else f"--workload {a.workload}")
     lines = [f"# Kernel time per {unit}: {wl}", "", "Command (MI355X, repository root copied to `<repo>`):", "", "```",
