@@ -16,6 +16,7 @@
 #include <string>
 #include <vector>
 
+#include "live_bound.h"
 #include "recis_mi355x.h"
 #include "rs_internal.h"
 
@@ -241,16 +242,10 @@ struct rs_table {
   uint32_t clock = 0;
   int64_t* free_rows = nullptr;
   int64_t free_cap = 0;
-  // host view of the live count: an upper bound.  Every insert call gets a
-  // 16-bit tag; its compaction kernel stores (tag << 48) | exact live count into
-  // h_pin[0], and bound_after[tag % kTags] remembers the host's bound right
-  // after that call was enqueued, so a published count refreshes the bound
-  // by the calls enqueued since (bound_after[.] = -1: no refresh from it).
-  static constexpr int kTags = 64;
-  int64_t live_bound = 0;
+  // host view of the live count, refreshed from the words that the insert
+  // calls' kernels publish to h_pin[0]
+  LiveBound live;
   int64_t* h_pin = nullptr;
-  int64_t tag = 0;
-  int64_t bound_after[kTags];
   int64_t adam_t = 0;
   // internal workspace for ht_find_or_insert
   void* iws = nullptr;
@@ -437,30 +432,8 @@ rs_status grow_for(rs_table* t, int64_t keys_need, int64_t tombs, int64_t rows_n
   return provision_rows(t, std::min(rows_need, t->limit), s);
 }
 
-// Lower the host's bound on live rows with the newest count a compaction kernel
-// has published (calls enqueued after it keep their share of the bound).
-void refresh_bound(rs_table* t) {
-  const int64_t v = __atomic_load_n(t->h_pin, __ATOMIC_ACQUIRE);
-  const int64_t tag = (v >> 48) & 0xFFFF;
-  if (tag == 0 || ((t->tag - tag) & 0xFFFF) >= rs_table::kTags) return;
-  const int64_t after = t->bound_after[tag % rs_table::kTags];
-  if (after < 0) return;
-  const int64_t exact = v & ((int64_t(1) << 48) - 1);
-  t->live_bound = std::min(t->live_bound, exact + (t->live_bound - after));
-}
-
-// The bound becomes exact (after a synchronization): counts published for
-// earlier calls can no longer refresh it.
-void reset_bound(rs_table* t, int64_t exact) {
-  t->live_bound = exact;
-  for (int64_t& b : t->bound_after) b = -1;
-}
-
-int64_t next_tag(rs_table* t) {
-  t->tag = (t->tag & 0xFFFF) == 0xFFFF ? 1 : t->tag + 1;  // tags 1..65535 (0: nothing published)
-  t->bound_after[t->tag % rs_table::kTags] = -1;
-  return t->tag;
-}
+// Lower the host's bound on live rows with the newest published count.
+void refresh_bound(rs_table* t) { t->live.refresh(__atomic_load_n(t->h_pin, __ATOMIC_ACQUIRE)); }
 
 void record_pair(hipEvent_t* ev, hipStream_t s) {
   if (ev && ev[0]) (void)hipEventRecord(ev[0], s);
@@ -473,24 +446,23 @@ void record_pair(hipEvent_t* ev, hipStream_t s) {
 rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const Work& w, bool occ_lists,
                            int64_t* rows_out, int64_t* n_inserted, hipStream_t s) {
   rs_status st = RS_OK;
-  int64_t tag = next_tag(t);
+  int64_t tag = t->live.next_tag();
   if (n > 0 && small_batch(n)) {
     // its front end reserves rows and inserts in one go: only where n new keys
     // are known to fit
     refresh_bound(t);
-    const int64_t after = t->live_bound + n;
+    const int64_t after = t->live.bound + n;
     if (after <= t->limit && after <= t->rows_prov) {
       RS_HIP(launch_small_front(values, n, t->dev(), w, occ_lists, t->h_pin, tag, rows_out, n_inserted,
                                 t->ev(RS_K_TILE_DEDUP), t->ev(RS_K_COMPACT_INSERT), s));
       for (int k : {RS_K_PARTITION, RS_K_INIT_ROWS, RS_K_OCC}) record_pair(t->ev(k), s);  // no launch of their own
-      t->live_bound = after;
-      t->bound_after[tag % rs_table::kTags] = after;
+      t->live.enqueued(n, after);
       return RS_OK;
     }
   }
   RS_HIP(launch_dedup_probe(values, n, t->dev(), w, t->ev(RS_K_TILE_DEDUP), t->ev(RS_K_PARTITION), s));
   refresh_bound(t);
-  const int64_t bound = t->live_bound + n;
+  const int64_t bound = t->live.bound + n;
   if (bound > t->limit || bound > t->rows_prov) {
     // exact decision: read back U and live (one synchronization)
     RS_HIP(hipStreamSynchronize(s));
@@ -510,19 +482,17 @@ rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const 
       const rs_status e2 = set_scalar(t, kTKeys, cs[kCBaseKeys], s);
       const rs_status e3 = set_scalar(t, kTFree, cs[kCFreeTop], s);
       if (e1 != RS_OK || e2 != RS_OK || e3 != RS_OK) return RS_EHIP;
-      reset_bound(t, std::max(cs[kCBaseKeys] + ts[kTTomb], cs[kCBaseLive]));
+      t->live.bound = std::max(cs[kCBaseKeys] + ts[kTTomb], cs[kCBaseLive]);
       return st;  // grow_for's message stays the last error
     }
     int64_t tombs = 0;
     RS_HIP(hipMemcpy(&tombs, t->d_scal + kTTomb, sizeof(int64_t), hipMemcpyDeviceToHost));
     // redo the reservation against the grown table
-    reset_bound(t, std::max(keys_need + tombs, rows_need));
-    tag = next_tag(t);
+    tag = t->live.next_tag();
     RS_HIP(launch_rereserve(w, t->dev(), s));
-    t->bound_after[tag % rs_table::kTags] = t->live_bound;
+    t->live.enqueued(n, std::max(keys_need + tombs, rows_need));
   } else {
-    t->live_bound = bound;
-    t->bound_after[tag % rs_table::kTags] = t->live_bound;
+    t->live.enqueued(n, bound);
   }
   RS_HIP(launch_compact_insert(values, n, t->dev(), w, occ_lists, t->h_pin, tag, t->ev(RS_K_COMPACT_INSERT),
                                t->ev(RS_K_INIT_ROWS), t->ev(RS_K_OCC), s));
@@ -629,7 +599,6 @@ rs_status ht_create(const rs_table_desc* d, const rs_allocator* a, rs_stream str
       break;
     }
     t->h_pin[0] = 0;
-    for (int64_t& b : t->bound_after) b = -1;
     if (hipMemsetAsync(t->slots, 0, sizeof(Slot) * static_cast<size_t>(t->cap), s) != hipSuccess ||
 
         hipMemsetAsync(t->d_scal, 0, sizeof(int64_t) * kTScalars, s) != hipSuccess) {
@@ -830,7 +799,7 @@ rs_status ht_size(rs_table* t, int64_t* live_host, rs_stream stream) {
   int64_t ts[kTScalars];
   RS_HIP(hipMemcpy(ts, t->d_scal, sizeof(ts), hipMemcpyDeviceToHost));
   *live_host = ts[kTKeys];
-  reset_bound(t, std::max(ts[kTKeys] + ts[kTTomb], ts[kTLive]));
+  t->live.bound = std::max(ts[kTKeys] + ts[kTTomb], ts[kTLive]);
   return take_latched(t);
 }
 
@@ -855,7 +824,7 @@ rs_status ht_evict(rs_table* t, uint32_t max_age, int64_t* n_evicted_host, rs_st
     st = fail(RS_EHIP, "eviction read-back failed");
   t->release(bcount);
   if (st != RS_OK) return st;
-  reset_bound(t, std::max(ts[kTKeys] + ts[kTTomb], ts[kTLive]));
+  t->live.bound = std::max(ts[kTKeys] + ts[kTTomb], ts[kTLive]);
   if (n_evicted_host) *n_evicted_host = n;
   return take_latched(t);
 }
@@ -918,7 +887,7 @@ rs_status ht_compact(rs_table* t, int64_t* moved_host, int64_t* bytes_released_h
   rs_status st = set_scalar(t, kTRowCap, t->rows_prov, s);
   if (st != RS_OK) return st;
   RS_HIP(hipStreamSynchronize(s));
-  reset_bound(t, std::max(L + ts[kTTomb], L));
+  t->live.bound = std::max(L + ts[kTTomb], L);
   if (moved_host) *moved_host = moved;
   if (bytes_released_host) *bytes_released_host = released;
   return take_latched(t);

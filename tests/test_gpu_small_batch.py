@@ -90,3 +90,20 @@ def test_small_batch_reserved_keys_evictions_and_find_or_insert():
     rows = rows.cpu().numpy()
     assert rows[1] == -1 and rows[3] == -1 and rows[0] == rows[4] >= 0 and rows[2] >= 0
     gt.close()
+
+
+@pytest.mark.parametrize("max_load,slots,third", [(0.6, 1 << 13, 3000), (0.75, 1 << 13, 5000)])
+def test_batch_past_the_small_limit_grows_the_table(max_load, slots, third):
+    """A batch of at most 8192 ids that may not fit takes the general front end, which reads the published count
+    again: the table still grows and every key gets a row."""
+    t = R.Table(8, R.F32, R.ADAGRAD, capacity_slots=slots, max_load=max_load, block_rows=1 << 13, seed=3)
+    first = torch.arange(2000, dtype=torch.int64, device="cuda")
+    new = torch.arange(10000, 10000 + third, dtype=torch.int64, device="cuda")
+    for keys, want in ((first, 2000), (first, 0), (new, third), (new, 0)):
+        rows, nins = t.find_or_insert(keys)
+        torch.cuda.synchronize()  # the call's count is published before the next one reads it
+        print("bound", keys.numel(), int(nins.item()), flush=True)
+        assert int(nins.item()) == want and int(rows.min().item()) >= 0
+    assert t.size() == 2000 + third and t.capacity() > slots
+    t.check()
+    t.close()

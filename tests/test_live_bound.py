@@ -1,0 +1,117 @@
+"""The host's bound on the live count (csrc/live_bound.h), driven on the CPU.
+
+A model of the device: calls queue up, each inserts at most its ids, and
+publishes (tag << 48) | live count when it runs.  Whatever published word the
+host reads, however often, the bound must not fall below the live count that
+the queued calls lead to; it must be exact once the newest call has published.
+"""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2509_20883_amd import recis as R
+
+SHIM = r'''
+#include "live_bound.h"
+static rs::LiveBound b;
+extern "C" {
+void fresh() { b = rs::LiveBound(); }
+int64_t next_tag() { return b.next_tag(); }
+void enqueued(int64_t n, int64_t after) { b.enqueued(n, after); }
+void refresh(int64_t w) { b.refresh(w); }
+void set_bound(int64_t v) { b.bound = v; }
+int64_t bound() { return b.bound; }
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def lb(tmp_path_factory):
+    d = tmp_path_factory.mktemp("live_bound")
+    (d / "shim.cpp").write_text(SHIM)
+    so = str(d / "shim.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
+                    os.path.join(R.PKG, "csrc"), str(d / "shim.cpp"), "-o", so], check=True)
+    L = C.CDLL(so)
+    L.next_tag.restype = L.bound.restype = C.c_int64
+    L.enqueued.argtypes = [C.c_int64, C.c_int64]
+    L.refresh.argtypes = L.set_bound.argtypes = [C.c_int64]
+    return L
+
+
+def _word(tag, live):
+    w = (tag << 48) | live
+    return w - (1 << 64) if w >= 1 << 63 else w
+
+
+def test_a_published_count_read_twice(lb):
+    """2000 new keys, the same 2000 again, then 3000 new ones: the third call reads the same word twice."""
+    lb.fresh()
+    for live in (2000, 2000):  # both calls have run before the third
+        t = lb.next_tag()
+        lb.refresh(_word(t - 1, 2000) if t > 1 else 0)
+        lb.enqueued(2000, lb.bound() + 2000)
+        word = _word(t, live)
+    assert lb.bound() == 4000
+    lb.next_tag()
+    lb.refresh(word)
+    lb.refresh(word)
+    assert lb.bound() == 2000
+    lb.enqueued(3000, lb.bound() + 3000)
+    assert lb.bound() == 5000
+
+
+def test_an_old_count_read_again_with_calls_in_flight(lb):
+    """Call 1 (100 ids, 10 new) has published; calls 2 and 3 (100 new keys each) are queued."""
+    lb.fresh()
+    t1 = lb.next_tag()
+    lb.enqueued(100, 100)
+    for _ in range(2):
+        lb.next_tag()
+        lb.refresh(_word(t1, 10))
+        lb.enqueued(100, lb.bound() + 100)
+    for _ in range(3):
+        lb.refresh(_word(t1, 10))
+        assert lb.bound() == 210
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_bound_never_below_the_live_count(lb, seed):
+    g = np.random.default_rng(seed)
+    lb.fresh()
+    queue, words = [], [0]  # calls not yet run: (tag, new keys); words published so far
+    device, total = 0, 0    # live count on the device; once every queued call has run
+
+    def step_device():
+        nonlocal device
+        tag, new = queue.pop(0)
+        device += new
+        words.append(_word(tag, device))
+
+    for it in range(70000 if seed == 0 else 3000):  # seed 0: the tags wrap
+        if g.random() < 0.002:  # a synchronizing call: the exact count
+            while queue:
+                step_device()
+            lb.set_bound(device)
+        n = int(g.integers(1, 5000))
+        new = int(n * g.random()) if g.random() < 0.5 else n * int(g.integers(0, 2))
+        tag = lb.next_tag()
+        for _ in range(int(g.integers(0, 4))):
+            while queue and g.random() < 0.5:
+                step_device()
+            # the newest word, or a late reader's older one
+            lb.refresh(words[-1 if g.random() < 0.8 else -min(len(words), int(g.integers(1, 6)))])
+            assert lb.bound() >= total, it
+        lb.enqueued(n, lb.bound() + n)
+        queue.append((tag, new))
+        total += new
+        assert lb.bound() >= total, it
+        if len(queue) > 40:
+            step_device()
+    while queue:
+        step_device()
+    lb.refresh(words[-1])
+    assert lb.bound() == total
