@@ -363,9 +363,7 @@ rs_status lookup_pool_bwd_opt(rs_table* t, const rs_ctx* ctx, const void* grad_o
  *                shard_offsets[nshards] = U
  *   inverse [n] int32: keys_out[inverse[i]] == values[i]; -1 for a reserved
  *                key (INT64_MIN, INT64_MIN+1), which takes no part
- *   info [2] int64: {U, error bits}: bit 0 (1) a reserved key was skipped;
- *                bit 3 (8) an internal dedup pass overflowed (outputs
- *                invalid; not expected for any input)
+ *   info [2] int64: {U, error bits}: bit 0 (1) a reserved key was skipped
  * values [n] int64, n <= 2^28; 1 <= nshards <= 1024.  workspace: device,
  * 256-byte aligned, >= ids_partition_workspace_bytes(n, nshards) bytes,
  * reusable by the next call once this one has completed in stream order.

@@ -377,11 +377,13 @@ __device__ inline int64_t resolve_probe(const TableDev& t, unsigned long long e,
 // compaction read again: this pass 399 us for 16.4M ids of 3.8M keys, then 331,
 // the sums 70 and 33, the compaction 160 and 106; 167 / 134, 31 / 13 and 48 /
 // 49 for 10.6M ids of 1.4M keys).
-// A partition of at most kPartSlots records is done in one pass with each
-// thread's records in registers (its distinct keys always fit the table);
-// a larger one in sweeps of at most kPartSweep records by a hash of the key,
-// and if a sweep's keys do not fit (a skewed hash) the partition starts
-// again with twice as many sweeps.
+// A partition of at most kPartThreads * kPartFast = 2560 records is done in one
+// pass with each thread's records in registers; a larger one, or one with more
+// than kPartSlots = 2048 distinct keys, in sweeps of about kPartSweep records by
+// a hash of the key, and if a sweep's keys do not fit (a skewed hash) the
+// partition starts again with twice as many sweeps.  Where kMaxSweeps sweeps do
+// not help either, rounds take as many keys as fit, so every partition ends
+// with a result for each of its records.
 
 // IDMap rows of the d keys listed in cdense; a key's row replaces it in the table.
 __device__ inline void probe_keys(const TableDev& t, int d, const short* cdense, unsigned long long* ckey) {
@@ -419,6 +421,8 @@ __device__ inline int lds_insert(unsigned long long* ckey, unsigned long long e,
   }
   return -1;
 }
+
+constexpr int kRoundProbes = 64;  // probe window of a round (full windows cost as many steps per record and round)
 
 __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w, int64_t n) {
   constexpr int NT = kPartThreads, S = kPartSlots, OWN = S / NT, K = kPartFast;
@@ -508,9 +512,8 @@ __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w,
   };
   bool fresh = true;  // the LDS table is clear
   if (nr <= NT * K) {
-    // one pass: the thread's records tid, tid + NT, ... stay in registers
-    // (up to kPartSlots records their keys always fit the table; beyond, a
-    // full table sends the partition to the sweeps)
+    // one pass: the thread's records tid, tid + NT, ... stay in registers (more
+    // than kPartSlots distinct keys fill the table: on to the sweeps)
     int pos[K];
     TileRec x[K];
 #pragma unroll
@@ -548,6 +551,59 @@ __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w,
     fresh = false;
     __syncthreads();  // every thread has read ovf before the sweeps reset it
   }
+
+  // Rounds: ids whose hashes agree in the partition's bits and in the sweeps'
+  // (they have to be made so: the hash can be inverted) do not fit any sweep.
+  // A round enters keys, by another hash, until a key finds its probe window
+  // full.  No slot is emptied in a round, so if one record of a key finds no
+  // slot all its records find none: they wait for the next round.  Each round
+  // takes at least its first record's key, so the rounds end.
+  auto rounds = [&]() {
+    constexpr int kToDo = -1, kDone = -2;
+    for (int f = tid; f < nr; f += NT) w.ptmp[rec_pos(f)].x = kToDo;
+    bool more = true;
+    while (more) {
+      __syncthreads();  // every thread is done with the LDS (and with ovf)
+      for (int q = tid; q < S; q += NT) {
+        ckey[q] = kEncEmpty;
+        cfp[q] = ~0u;
+        ccnt[q] = 0u;
+      }
+      if (tid == 0) ovf = 0;
+      __syncthreads();
+      for (int f = tid; f < nr; f += NT) {
+        const int pos = rec_pos(f);
+        if (w.ptmp[pos].x != kToDo) continue;
+        const TileRec x = w.srec[pos];
+        unsigned int sl = static_cast<unsigned int>(idmap_hash(x.key) >> 20) & (S - 1);
+        bool in = false;
+#pragma unroll 1
+        for (int probes = 0; probes < kRoundProbes && !in; ++probes) {
+          const unsigned long long old = atomicCAS(&ckey[sl], kEncEmpty, x.key);
+          in = old == kEncEmpty || old == x.key;
+          if (!in) sl = (sl + 1) & (S - 1);
+        }
+        if (!in) {
+          ovf = 1;
+          continue;
+        }
+        atomicMin(&cfp[sl], x.src);
+        w.ptmp[pos] = make_int2(static_cast<int>(sl), static_cast<int>(atomicAdd(&ccnt[sl], x.meta + 1u)));
+      }
+      __syncthreads();
+      more = ovf != 0;
+      for (int f = tid; f < nr; f += NT) {
+        const int pos = rec_pos(f);
+        const int2 tp = w.ptmp[pos];
+        if (tp.x < 0) continue;
+        const TileRec x = w.srec[pos];
+        if (lookup && cfp[tp.x] == x.src)  // the key's first record alone carries its row
+          ckey[tp.x] = static_cast<unsigned long long>(idmap_lookup(t, x.key));
+        result(x.src, x.key, tp.x, static_cast<unsigned int>(tp.y));
+        w.ptmp[pos].x = kDone;
+      }
+    }
+  };
 
   // sweeps: a partition above the register pass (ids that hardly repeat, or a
   // skewed hash).  Sweep s takes the keys whose 20 hash bits mod nsw are s (a
@@ -596,8 +652,8 @@ __global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w,
     __syncthreads();
     if (ovf) {
       __syncthreads();  // every thread has read ovf
-      if (nsw >= kMaxSweeps) {
-        if (tid == 0) atomicOr(reinterpret_cast<int*>(&t.scal[kTErr]), kErrProbe);
+      if (__builtin_expect(nsw >= kMaxSweeps, 0)) {
+        rounds();
         return;
       }
       nsw *= 2;
@@ -1091,7 +1147,7 @@ __device__ inline void occ_pass(const Work& w, int64_t n, uint32_t blk) {
   for (int k = 0; k < 4; ++k) {
     const uint32_t o = static_cast<uint32_t>(ow[k]);
     const uint32_t kidx = rr[k].y & kRecFirst ? base + (o >> 12) : rr[k].x;
-    // in range also where an overflowed partition left no result
+    // (clamped: no result could become a wild read)
     a[k] = w.kinfo[o == kOccRejected ? 0u : min(kidx, static_cast<uint32_t>(w.nkeyidx - 1))];
   }
   int pos[4];
