@@ -483,8 +483,10 @@ __global__ __launch_bounds__(kBlock) void k_bwd_long_finish(TableDev t, Work w, 
 // lane group: the keys' finishes, each a chain of dependent loads, then run on
 // as many blocks (with the units of ten keys in one block they followed each
 // other: 34 us for the launch, 4750 ids).  The partial rows travel as
-// agent-scope accesses, complete (vmcnt 0) before their count: a device-scope
-// release fence would write back the L2.  4750 ids, dim 16: 8.0 us; the list,
+// agent-scope accesses, complete before their count: on gfx950 an agent-scope
+// store has reached the memory that all XCDs see when vmcnt counts it done, and
+// an agent-scope load reads there.  This rests on the hardware, not on the
+// language's memory model: its device-scope release fence would write back the L2.  4750 ids, dim 16: 8.0 us; the list,
 // short-key, unit and finish launches took 8.4 + 8.2 + 4.4 + 4.5 us.
 template <typename WT, typename GT, int LANES, int MODE, bool FUSED>
 __global__ __launch_bounds__(kBlock) void k_bwd_small(TableDev t, Work w, uint32_t nref, const GT* __restrict__ grad,
@@ -506,7 +508,9 @@ __global__ __launch_bounds__(kBlock) void k_bwd_small(TableDev t, Work w, uint32
     sum_unit<GT, E, LANES, MODE>(w, grad, nref, un, lane, acc);
     store_agent<E>(w.gpart + unit * D + lane * E, acc);
     const int nu = unit_count(w.useg[w.long_u[un.li]].count, w.maxu);
-    __builtin_amdgcn_s_waitcnt(0);  // the partial row (one wave's) is complete
+    // the partial row (one wave's) is complete before its count; the clobber
+    // keeps the compiler from moving the stores past the wait
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (lane == 0) {
       const bool last = atomicAdd(&w.id_ref[un.li], 1) == nu - 1;
       if (last) w.id_ref[un.li] = 0;  // ready for another backward of this context

@@ -107,3 +107,51 @@ def test_batch_past_the_small_limit_grows_the_table(max_load, slots, third):
     assert t.size() == 2000 + third and t.capacity() > slots
     t.check()
     t.close()
+
+
+@pytest.mark.parametrize("dim", [8, 16, 32, 64, 128, 256])
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("mode", [W.SUM, W.MEAN, W.NONE, W.TAIL])
+def test_small_batch_at_every_width_and_backward_again(dim, dtype, mode):
+    """Lane groups of 1 to 64 lanes, fp32 and bf16 rows and gradients; keys of one to ten hot-key units.  A context's
+    backward can run again (the counter of a key's finished units starts over): two-call sums twice, then fused."""
+    print("small batch width", dim, dtype, mode, flush=True)
+    w = W.workload(0)
+    w.dim, w.row_dtype, w.mode, w.capacity_slots = dim, dtype, mode, 1 << 14
+    w.grad_dtype = dtype if W.padded(mode) else W.F32
+    w.pad_len = 13 if W.padded(mode) else 0
+    g = np.random.default_rng(dim)
+    gt, ot = P.gpu_table(w), P.oracle_table(w)
+    for step in range(2):  # the first on the general front end (a new table), the second on the two launches
+        off = np.concatenate([[0], np.cumsum(g.integers(0, 20, size=250))]).astype(np.int64)
+        n = int(off[-1])
+        ids = np.concatenate([np.full(c, 7 + i) for i, c in enumerate((33, 64, 65, 320))] +
+                             [g.integers(100, 100 + n, size=n)])[:n]
+        b = W.Batch(values=g.permutation(ids), offsets=off, n_features=1, batch=250)
+        grad = W.make_grad(w, b, step)
+        P.run_step_parity(w, gt, ot, b, grad, step)
+        # the same batch again, every key known: sums twice, then the fused update
+        _, _, ctx = gt.forward(P.to_dev(b.values), P.to_dev(off), mode, pad_len=w.pad_len)
+        _, uniq, inv = O.dedup(b.values)
+        U = uniq.size
+        ref = O.backward(off, inv, U, dim, mode, w.pad_len, grad)
+        mag = O.backward(off, inv, U, dim, mode, w.pad_len, np.abs(grad))
+        gd = P.to_dev(grad)
+        if w.grad_dtype == W.BF16:
+            gd = gd.to(torch.bfloat16)
+        for again in range(2):
+            P.assert_sum_close(gt.backward(ctx, gd)[:U].cpu().numpy(), ref, mag, what=f"backward {again}")
+        w0, s0 = (x.cpu().numpy() for x in gt.read_rows(ctx.rows(U)))
+        gt.backward_optimizer(ctx, gd, w.lr, w.eps)
+        w1, s1 = (x.cpu().numpy() for x in gt.read_rows(ctx.rows(U)))
+        ot.write_rows(uniq, w0, s0)
+        _, rows, _ = ot.find_or_insert(uniq)
+        ot.optimizer(rows, ref.astype(np.float32), w.lr, w.eps)
+        _, w_ref, s_ref = ot.read_rows(uniq)
+        dg = 1e-5 * mag + np.abs(ref) * 2.0 ** -23
+        P.assert_opt_close(w1, s1, w_ref, s_ref,
+                           P.opt_bounds(w.opt, dtype, w0, s0, ref, dg, w.lr, w.eps, w.beta1, w.beta2, ot.t, w_ref),
+                           what="fused update")
+        ot.write_rows(uniq, w1, s1)
+    gt.check()
+    gt.close()
