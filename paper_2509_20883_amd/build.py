@@ -8,6 +8,9 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "librecis_mi355x.so")
 SOURCES = ["dedup_idmap.hip", "ids_partition.hip", "feature_ops.hip", "pool.hip", "backward.hip", "probes.hip", "ids_static.hip", "api.hip"]
+# sources compiled once per part (-DRS_PART=k): a part is a code object of its
+# own, loaded when a process first launches one of its kernels
+PARTS = {"pool.hip": 4, "backward.hip": 5}
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -25,10 +28,10 @@ def build(verbose: bool = False, jobs: int = 4, out: str = LIB, defines=()) -> s
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
     procs = []
-    for src in SOURCES:
-        obj = out + "." + src + ".o"
-        cmd = [hipcc, *HIPCC_FLAGS, *[f"-D{d}" for d in defines], "-c", "-I", os.path.join(ROOT, "include"), "-I",
-               CSRC, os.path.join(CSRC, src), "-o", obj]
+    for src, part in [(src, k) for src in SOURCES for k in range(PARTS.get(src, 1))]:
+        obj = f"{out}.{src}.{part}.o"
+        cmd = [hipcc, *HIPCC_FLAGS, f"-DRS_PART={part}", *[f"-D{d}" for d in defines], "-c", "-I",
+               os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(CSRC, src), "-o", obj]
         cmd.remove("-shared")
         if verbose:
             print(" ".join(cmd), flush=True)

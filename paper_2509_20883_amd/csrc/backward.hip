@@ -24,6 +24,10 @@
 // A small batch takes both strategies and the finish in one launch
 // (k_bwd_small).  Without the optimizer (lookup_pool_bwd) the same kernels
 // write grad_unique.
+//
+// Compiled once per part (RS_PART: 0 what the others share, 1-4 row type x
+// optimizer fused or not), each part a code object of its own: a process loads
+// only the parts it uses (pool.hip has the figures).
 #include "device_common.h"
 
 #include <hip/hip_ext.h>
@@ -521,6 +525,99 @@ __global__ __launch_bounds__(kBlock) void k_bwd_small(TableDev t, Work w, uint32
   if (done) finish_key<WT, E, LANES, FUSED, true>(t, w, un.li, grad_unique, o, red);
 }
 
+// Unit sums of the hot keys of n ids, one lane group per possible unit (the
+// device-side count is at most 2n/kUnit + 2): no group takes a second unit
+// while others are idle.
+template <typename GT, int LANES, int MODE>
+void units_launch(const Work& w, uint32_t nref, int64_t n, const GT* grad, hipEvent_t start, hipStream_t s);
+
+template <typename WT, typename GT, int LANES, int MODE, bool FUSED>
+static hipError_t bwd_launch(const TableDev& t, const Work& w, uint32_t nref, int64_t n, const void* grad,
+                             float* gu, const OptArgs& o, hipEvent_t* ev_s, hipEvent_t* ev_l, hipStream_t s) {
+  constexpr int E = 16 / static_cast<int>(sizeof(GT));
+  constexpr int GPB = kBlock / LANES;
+  const GT* g = static_cast<const GT*>(grad);
+  // grid-stride loops over device-side counts (U, units, hot keys): a grid
+  // of at most kResident blocks per strategy keeps every CU busy without
+  // dispatching wavefronts that would find no work
+  // optional timing events are timestamped by the dispatches themselves
+  // (short keys: their kernel; hot keys: unit sums start to finish end)
+  hipEvent_t s0 = ev_s ? ev_s[0] : nullptr, s1 = ev_s ? ev_s[1] : nullptr;
+  hipEvent_t l0 = ev_l ? ev_l[0] : nullptr, l1 = ev_l ? ev_l[1] : nullptr;
+  if (small_batch(n)) {  // one launch; the hot-key events have nothing of their own to bracket
+    const unsigned sb = grid_for(n, GPB, kResident), ub = static_cast<unsigned>(2 * (n / kUnit) + 2);
+    hipExtLaunchKernelGGL((k_bwd_small<WT, GT, LANES, MODE, FUSED>), dim3(sb + ub), dim3(kBlock), 0, s, s0, s1, 0, t, w,
+                          nref, g, gu, o, static_cast<int>(sb));
+    if (l0) (void)hipEventRecord(l0, s);
+    if (l1) (void)hipEventRecord(l1, s);
+    return hipGetLastError();
+  }
+  hipExtLaunchKernelGGL((k_bwd_short<WT, GT, LANES, MODE, FUSED>), dim3(grid_for(n, GPB, kResident)), dim3(kBlock), 0,
+                        s, s0, s1, 0, t, w, nref, g, gu, o);
+  units_launch<GT, LANES, MODE>(w, nref, n, g, l0, s);
+  hipExtLaunchKernelGGL((k_bwd_long_finish<WT, E, LANES, FUSED>), dim3(grid_for(n / kLong + 1, 1, 4 * kResident)),
+                        dim3(kBlock), 0, s, nullptr, l1, 0, t, w, gu, o);
+  return hipGetLastError();
+}
+
+#define RS_BWD_ARGS                                                                                                     \
+  const TableDev &t, const Work &w, uint32_t nref, int64_t n, int mode, const void *grad, float *gu, const OptArgs &o,   \
+      hipEvent_t *es, hipEvent_t *el, hipStream_t s
+
+// dim 8 ... 256: 2 to 64 lanes of fp32 gradients, 1 to 32 of bf16 ones
+template <typename WT, typename GT, int MODE, bool FUSED>
+static hipError_t bwd_dim(RS_BWD_ARGS) {
+  constexpr int E = 16 / static_cast<int>(sizeof(GT));
+  switch (t.dim) {
+    case 8: return bwd_launch<WT, GT, 8 / E, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
+    case 16: return bwd_launch<WT, GT, 16 / E, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
+    case 32: return bwd_launch<WT, GT, 32 / E, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
+    case 64: return bwd_launch<WT, GT, 64 / E, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
+    case 128: return bwd_launch<WT, GT, 128 / E, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
+    case 256: return bwd_launch<WT, GT, 256 / E, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// Backward of rows of type WT, with or without the optimizer.
+template <typename WT, bool FUSED>
+hipError_t bwd_part(RS_BWD_ARGS) {
+  if (mode == 2 || mode == 3) return bwd_dim<WT, WT, 0, FUSED>(t, w, nref, n, mode, grad, gu, o, es, el, s);
+  if (mode == 1) return bwd_dim<WT, float, 1, FUSED>(t, w, nref, n, mode, grad, gu, o, es, el, s);
+  return bwd_dim<WT, float, 0, FUSED>(t, w, nref, n, mode, grad, gu, o, es, el, s);
+}
+
+#if RS_PART == 1
+template hipError_t bwd_part<float, true>(RS_BWD_ARGS);
+#elif RS_PART == 2
+template hipError_t bwd_part<float, false>(RS_BWD_ARGS);
+#elif RS_PART == 3
+template hipError_t bwd_part<uint16_t, true>(RS_BWD_ARGS);
+#elif RS_PART == 4
+template hipError_t bwd_part<uint16_t, false>(RS_BWD_ARGS);
+#endif
+
+#if RS_PART == 0
+extern template hipError_t bwd_part<float, true>(RS_BWD_ARGS);
+extern template hipError_t bwd_part<float, false>(RS_BWD_ARGS);
+extern template hipError_t bwd_part<uint16_t, true>(RS_BWD_ARGS);
+extern template hipError_t bwd_part<uint16_t, false>(RS_BWD_ARGS);
+
+template <typename GT, int LANES, int MODE>
+void units_launch(const Work& w, uint32_t nref, int64_t n, const GT* grad, hipEvent_t start, hipStream_t s) {
+  hipExtLaunchKernelGGL((k_bwd_long<GT, LANES, MODE>),
+                        dim3((grid_for(2 * (n / kUnit) + 2, kBlock / LANES) + 7) / 8 * 8), dim3(kBlock), 0, s, start,
+                        nullptr, 0, w, nref, grad);
+}
+#define RS_UNITS(GT, LANES, MODE) \
+  template void units_launch<GT, LANES, MODE>(const Work&, uint32_t, int64_t, const GT*, hipEvent_t, hipStream_t);
+#define RS_UNITS_OF(GT, L0, MODE) \
+  RS_UNITS(GT, L0, MODE) RS_UNITS(GT, L0 * 2, MODE) RS_UNITS(GT, L0 * 4, MODE) RS_UNITS(GT, L0 * 8, MODE) \
+      RS_UNITS(GT, L0 * 16, MODE) RS_UNITS(GT, L0 * 32, MODE)
+RS_UNITS_OF(float, 2, 0)
+RS_UNITS_OF(float, 2, 1)
+RS_UNITS_OF(uint16_t, 1, 0)
+
 // The occurrence list the backward reads: position occ_pos[i] of id i
 // receives the gradient row the pool gave that id (id_ref).  Ids outside
 // the pooled range [lo, hi) get no gradient row (-1); ids of a rejected key
@@ -624,64 +721,6 @@ __global__ __launch_bounds__(kOccListNT) void k_occ_list(Work w, int64_t n) {
   }
 }
 
-template <typename WT, typename GT, int LANES, int MODE, bool FUSED>
-static hipError_t bwd_launch(const TableDev& t, const Work& w, uint32_t nref, int64_t n, const void* grad,
-                             float* gu, const OptArgs& o, hipEvent_t* ev_s, hipEvent_t* ev_l, hipStream_t s) {
-  constexpr int E = 16 / static_cast<int>(sizeof(GT));
-  constexpr int GPB = kBlock / LANES;
-  const GT* g = static_cast<const GT*>(grad);
-  // grid-stride loops over device-side counts (U, units, hot keys): a grid
-  // of at most kResident blocks per strategy keeps every CU busy without
-  // dispatching wavefronts that would find no work
-  // optional timing events are timestamped by the dispatches themselves
-  // (short keys: their kernel; hot keys: unit sums start to finish end)
-  hipEvent_t s0 = ev_s ? ev_s[0] : nullptr, s1 = ev_s ? ev_s[1] : nullptr;
-  hipEvent_t l0 = ev_l ? ev_l[0] : nullptr, l1 = ev_l ? ev_l[1] : nullptr;
-  if (small_batch(n)) {  // one launch; the hot-key events have nothing of their own to bracket
-    const unsigned sb = grid_for(n, GPB, kResident), ub = static_cast<unsigned>(2 * (n / kUnit) + 2);
-    hipExtLaunchKernelGGL((k_bwd_small<WT, GT, LANES, MODE, FUSED>), dim3(sb + ub), dim3(kBlock), 0, s, s0, s1, 0, t, w,
-                          nref, g, gu, o, static_cast<int>(sb));
-    if (l0) (void)hipEventRecord(l0, s);
-    if (l1) (void)hipEventRecord(l1, s);
-    return hipGetLastError();
-  }
-  hipExtLaunchKernelGGL((k_bwd_short<WT, GT, LANES, MODE, FUSED>), dim3(grid_for(n, GPB, kResident)), dim3(kBlock), 0,
-                        s, s0, s1, 0, t, w, nref, g, gu, o);
-  // one lane group per possible unit (the device-side count is at most
-  // 2n/kUnit + 2): no group takes a second unit while others are idle
-  hipExtLaunchKernelGGL((k_bwd_long<GT, LANES, MODE>), dim3((grid_for(2 * (n / kUnit) + 2, GPB) + 7) / 8 * 8),
-                        dim3(kBlock), 0, s,
-                        l0, nullptr, 0, w, nref, g);
-  hipExtLaunchKernelGGL((k_bwd_long_finish<WT, E, LANES, FUSED>), dim3(grid_for(n / kLong + 1, 1, 4 * kResident)),
-                        dim3(kBlock), 0, s, nullptr, l1, 0, t, w, gu, o);
-  return hipGetLastError();
-}
-
-template <typename WT, typename GT, int MODE, bool FUSED>
-static hipError_t bwd_dim(const TableDev& t, const Work& w, uint32_t nref, int64_t n, const void* grad,
-                          float* gu, const OptArgs& o, hipEvent_t* es, hipEvent_t* el, hipStream_t s) {
-  constexpr int E = 16 / static_cast<int>(sizeof(GT));
-  switch (t.dim / E) {
-    case 1: return bwd_launch<WT, GT, 1, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-    case 2: return bwd_launch<WT, GT, 2, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-    case 4: return bwd_launch<WT, GT, 4, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-    case 8: return bwd_launch<WT, GT, 8, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-    case 16: return bwd_launch<WT, GT, 16, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-    case 32: return bwd_launch<WT, GT, 32, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-    case 64: return bwd_launch<WT, GT, 64, MODE, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-template <typename WT, bool FUSED>
-static hipError_t bwd_mode(const TableDev& t, const Work& w, uint32_t nref, int64_t n, int mode,
-                           const void* grad, float* gu, const OptArgs& o, hipEvent_t* es, hipEvent_t* el,
-                           hipStream_t s) {
-  if (mode == 2 || mode == 3) return bwd_dim<WT, WT, 0, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-  if (mode == 1) return bwd_dim<WT, float, 1, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-  return bwd_dim<WT, float, 0, FUSED>(t, w, nref, n, grad, gu, o, es, el, s);
-}
-
 hipError_t launch_bwd(const TableDev& t, const Work& w, int64_t nref, int64_t n, int mode, const void* grad,
                       float* grad_unique, const OptArgs* opt, hipEvent_t* ev_list, hipEvent_t* ev_short,
                       hipEvent_t* ev_long, hipStream_t s) {
@@ -697,11 +736,12 @@ hipError_t launch_bwd(const TableDev& t, const Work& w, int64_t nref, int64_t n,
     }
   }
   const OptArgs o = opt ? *opt : OptArgs{0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f, 0.f, 0.f};
+  const uint32_t nr = static_cast<uint32_t>(nref);
   if (opt)
-    return t.row_dtype ? bwd_mode<uint16_t, true>(t, w, static_cast<uint32_t>(nref), n, mode, grad, grad_unique, o, ev_short, ev_long, s)
-                       : bwd_mode<float, true>(t, w, static_cast<uint32_t>(nref), n, mode, grad, grad_unique, o, ev_short, ev_long, s);
-  return t.row_dtype ? bwd_mode<uint16_t, false>(t, w, static_cast<uint32_t>(nref), n, mode, grad, grad_unique, o, ev_short, ev_long, s)
-                     : bwd_mode<float, false>(t, w, static_cast<uint32_t>(nref), n, mode, grad, grad_unique, o, ev_short, ev_long, s);
+    return t.row_dtype ? bwd_part<uint16_t, true>(t, w, nr, n, mode, grad, grad_unique, o, ev_short, ev_long, s)
+                       : bwd_part<float, true>(t, w, nr, n, mode, grad, grad_unique, o, ev_short, ev_long, s);
+  return t.row_dtype ? bwd_part<uint16_t, false>(t, w, nr, n, mode, grad, grad_unique, o, ev_short, ev_long, s)
+                     : bwd_part<float, false>(t, w, nr, n, mode, grad, grad_unique, o, ev_short, ev_long, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -752,5 +792,7 @@ hipError_t launch_opt(const TableDev& t, const Work& w, int64_t n, const float* 
   if (ev && ev[1]) (void)hipEventRecord(ev[1], s);
   return e;
 }
+
+#endif  // RS_PART == 0
 
 }  // namespace rs

@@ -155,3 +155,52 @@ def test_small_batch_at_every_width_and_backward_again(dim, dtype, mode):
         ot.write_rows(uniq, w1, s1)
     gt.check()
     gt.close()
+
+
+@pytest.mark.parametrize("mode", [W.SUM, W.TAIL])
+def test_small_batch_with_reserved_keys(mode):
+    """A table with room, so the two launches see the rejected ids: no unique id, no row, no place in the list."""
+    w = W.workload(0)
+    w.mode, w.pad_len, w.capacity_slots = mode, 9 if W.padded(mode) else 0, 1 << 14
+    g = np.random.default_rng(2)
+    gt, ot = P.gpu_table(w), P.oracle_table(w)
+    gt.find_or_insert(torch.arange(8000, dtype=torch.int64, device="cuda"))  # provisions room for more
+    ot.find_or_insert(np.arange(8000))
+    off = np.concatenate([[0], np.cumsum(g.integers(0, 12, size=400))]).astype(np.int64)
+    n = int(off[-1])
+    ids = g.integers(0, 400, size=n)
+    ids[g.permutation(n)[:300]] = -2 ** 63
+    ids[g.permutation(n)[:300]] = -2 ** 63 + 1
+    b = W.Batch(values=ids, offsets=off, n_features=1, batch=400)
+    grad = W.make_grad(w, b, 0)
+    ctx = R.Ctx()
+    ctx.ensure(gt.workspace_bytes(n, 400), torch.device("cuda"))
+    ctx.ws.fill_(0xA5)
+    out, mask, ctx = gt.forward(P.to_dev(ids), P.to_dev(off), mode, pad_len=w.pad_len, ctx=ctx)
+    U = int(ctx.scalars()[0].item())
+    kept = ids > -2 ** 63 + 1
+    st, uniq, kept_inv = O.dedup(ids[kept])  # the oracle refuses a reserved key: the others, deduplicated
+    inv = np.full(n, -1, dtype=np.int32)
+    inv[kept] = kept_inv
+    assert st == O.OK and U == uniq.size and np.array_equal(ctx.unique(U).cpu().numpy(), uniq)
+    assert np.array_equal(ctx.inverse().cpu().numpy(), inv)
+    rows = np.concatenate([ot.read_rows(uniq)[1], np.zeros((1, w.dim), dtype=np.float32)])  # [-1]: nothing
+    o = out.cpu().numpy()
+    if W.padded(mode):
+        want, m = np.zeros_like(o), np.zeros((400, w.pad_len), dtype=np.uint8)
+        for i in range(400):
+            last = np.arange(off[i], off[i + 1])[-w.pad_len:]
+            want[i, :last.size], m[i, :last.size] = rows[inv[last]], 1
+        assert np.array_equal(o, want) and np.array_equal(mask.cpu().numpy(), m)
+    else:
+        bag = np.repeat(np.arange(400), np.diff(off))
+        want, mag = np.zeros(o.shape), np.zeros(o.shape)
+        np.add.at(want, bag, rows[inv].astype(np.float64))
+        np.add.at(mag, bag, np.abs(rows[inv]).astype(np.float64))
+        P.assert_sum_close(o, want, mag, what="pooled")
+    gu = gt.backward(ctx, P.to_dev(grad))[:U].cpu().numpy()
+    P.assert_sum_close(gu, O.backward(off, inv, U, w.dim, mode, w.pad_len, grad),
+                       O.backward(off, inv, U, w.dim, mode, w.pad_len, np.abs(grad)), what="grad_unique")
+    with pytest.raises(R.RecisError, match="RS_EKEY"):
+        gt.check()
+    gt.close()
