@@ -14,6 +14,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "live_bound.h"
@@ -432,8 +433,29 @@ rs_status grow_for(rs_table* t, int64_t keys_need, int64_t tombs, int64_t rows_n
   return provision_rows(t, std::min(rows_need, t->limit), s);
 }
 
-// Lower the host's bound on live rows with the newest published count.
-void refresh_bound(rs_table* t) { t->live.refresh(__atomic_load_n(t->h_pin, __ATOMIC_ACQUIRE)); }
+// Whether n more keys are known to fit the table.  A count that the bound still
+// misses is published by the front end of a call queued earlier, long before
+// that call's backward ends, so wait for the newest of them instead of draining
+// the stream: without the wait, two queued calls of a batch near the table's
+// headroom sent every call into the drain (the 1M-id tail step 159 -> 170 us).
+// Ends when the newest enqueued call has published or `s` has nothing to run.
+bool room_for(rs_table* t, int64_t n, hipStream_t s) {
+  constexpr int kPolls = 1024;
+  bool idle = false;
+  for (int polls = 1;; ++polls) {
+    const int64_t word = __atomic_load_n(t->h_pin, __ATOMIC_ACQUIRE);
+    t->live.refresh(word);
+    const int64_t after = t->live.bound + n;
+    if (after <= t->limit && after <= t->rows_prov) return true;
+    if (idle || t->live.settled(word)) return false;
+    std::this_thread::yield();
+    if (polls % kPolls == 0) {
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipErrorNotReady) (void)hipGetLastError();
+      idle = e != hipErrorNotReady;
+    }
+  }
+}
 
 void record_pair(hipEvent_t* ev, hipStream_t s) {
   if (ev && ev[0]) (void)hipEventRecord(ev[0], s);
@@ -446,24 +468,22 @@ void record_pair(hipEvent_t* ev, hipStream_t s) {
 rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const Work& w, bool occ_lists,
                            int64_t* rows_out, int64_t* n_inserted, hipStream_t s) {
   rs_status st = RS_OK;
+  if (n == 0) {  // no ids (a forward): the scalars alone; nothing to publish
+    RS_HIP(launch_dedup_probe(values, n, t->dev(), w, nullptr, nullptr, s));
+    return RS_OK;
+  }
   int64_t tag = t->live.next_tag();
-  if (n > 0 && small_batch(n)) {
-    // its front end reserves rows and inserts in one go: only where n new keys
-    // are known to fit
-    refresh_bound(t);
-    const int64_t after = t->live.bound + n;
-    if (after <= t->limit && after <= t->rows_prov) {
-      RS_HIP(launch_small_front(values, n, t->dev(), w, occ_lists, t->h_pin, tag, rows_out, n_inserted,
-                                t->ev(RS_K_TILE_DEDUP), t->ev(RS_K_COMPACT_INSERT), s));
-      for (int k : {RS_K_PARTITION, RS_K_INIT_ROWS, RS_K_OCC}) record_pair(t->ev(k), s);  // no launch of their own
-      t->live.enqueued(n, after);
-      return RS_OK;
-    }
+  // a small batch's front end reserves rows and inserts in one go: only where n
+  // new keys are known to fit
+  if (small_batch(n) && room_for(t, n, s)) {
+    RS_HIP(launch_small_front(values, n, t->dev(), w, occ_lists, t->h_pin, tag, rows_out, n_inserted,
+                              t->ev(RS_K_TILE_DEDUP), t->ev(RS_K_COMPACT_INSERT), s));
+    for (int k : {RS_K_PARTITION, RS_K_INIT_ROWS, RS_K_OCC}) record_pair(t->ev(k), s);  // no launch of their own
+    t->live.enqueued(n, t->live.bound + n);
+    return RS_OK;
   }
   RS_HIP(launch_dedup_probe(values, n, t->dev(), w, t->ev(RS_K_TILE_DEDUP), t->ev(RS_K_PARTITION), s));
-  refresh_bound(t);
-  const int64_t bound = t->live.bound + n;
-  if (bound > t->limit || bound > t->rows_prov) {
+  if (!room_for(t, n, s)) {
     // exact decision: read back U and live (one synchronization)
     RS_HIP(hipStreamSynchronize(s));
     // the scan already reserved rows for the keys not found (or as many as
@@ -492,7 +512,7 @@ rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const 
     RS_HIP(launch_rereserve(w, t->dev(), s));
     t->live.enqueued(n, std::max(keys_need + tombs, rows_need));
   } else {
-    t->live.enqueued(n, bound);
+    t->live.enqueued(n, t->live.bound + n);
   }
   RS_HIP(launch_compact_insert(values, n, t->dev(), w, occ_lists, t->h_pin, tag, t->ev(RS_K_COMPACT_INSERT),
                                t->ev(RS_K_INIT_ROWS), t->ev(RS_K_OCC), s));

@@ -17,7 +17,8 @@ namespace rs {
 struct LiveBound {
   static constexpr int kTags = 64;
   int64_t bound = 0;
-  int64_t tag = 0;  // the newest call's, 1 ... 65535 (0: nothing published)
+  int64_t tag = 0;   // the newest call's, 1 ... 65535 (0: nothing published)
+  int64_t last = 0;  // the newest enqueued call's
   int64_t ids = 0;  // ids of all enqueued calls
   int64_t ids_at[kTags];
 
@@ -34,8 +35,12 @@ struct LiveBound {
   void enqueued(int64_t n, int64_t after) {
     ids += n;
     ids_at[tag % kTags] = ids;
+    last = tag;
     bound = after;
   }
+
+  // No enqueued call has yet to publish: the bound can fall no further.
+  bool settled(int64_t word) const { return last == 0 || ((word >> 48) & 0xFFFF) == last; }
 
   // Lower the bound with a published word.
   void refresh(int64_t word) {

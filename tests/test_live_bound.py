@@ -11,6 +11,7 @@ import subprocess
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2509_20883_amd import recis as R
 
@@ -115,3 +116,32 @@ def test_bound_never_below_the_live_count(lb, seed):
         step_device()
     lb.refresh(words[-1])
     assert lb.bound() == total
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [6000, 20000])
+def test_queued_calls_do_not_drain_the_stream(n):
+    """A table with room for one more batch but not for two: a call behind a queued one waits for that one's published
+    count, not for the work queued behind it."""
+    t = R.Table(8, R.F32, R.ADAGRAD, capacity_slots=1 << 16, max_load=0.5, block_rows=1 << 14, seed=3)
+    live = (1 << 15) - n - 1000  # + n <= the limit of 2^15 keys, + 2 n above it
+    for part in torch.arange(live, device="cuda").split(4096):
+        t.find_or_insert(part)
+    keys = torch.arange(n, device="cuda") % live
+    t.reserve(1 << 15)
+    assert t.size() == live and t.capacity() == 1 << 16
+    x = torch.randn(4096, 4096, device="cuda")
+    torch.mm(x, x)
+    for _ in range(3):
+        torch.cuda.synchronize()
+        t.find_or_insert(keys)
+        for _ in range(200):
+            torch.mm(x, x)
+        behind = torch.cuda.Event()
+        behind.record()
+        rows, nins = t.find_or_insert(keys)
+        assert not behind.query(), "the call waited for the work queued before it"
+        assert int(nins.item()) == 0 and int(rows.min().item()) >= 0
+    assert t.capacity() == 1 << 16
+    t.check()
+    t.close()
