@@ -1,7 +1,7 @@
 """Both sides of the dispatch rules on batch size, against the oracle.
 
-The occurrence list is written by the pool up to 2^21 ids and by a launch of
-the backward above; a hot key has at most 4096 units in rows of dim <= 16 and
+The occurrence list is written by the pool (pooled or padded) up to 2^21 ids and
+by a launch of the backward above; a hot key has at most 4096 units in rows of dim <= 16 and
 1024 in wider ones (a key of 140,000 occurrences passes both limits); the ids
 partition keeps at most 2048 owner blocks (above 2^21 ids a block takes several
 record tiles) and scans up to 8192, up to 16384, or more counts.  Integers
@@ -38,6 +38,24 @@ def test_list_and_unit_limits(n, dim, mode):
     off = np.concatenate([[0], np.sort(g.integers(0, n + 1, size=bags - 1)), [n]]).astype(np.int64)
     b = W.Batch(values=_ids(n, g), offsets=off, n_features=1, batch=bags)
     P.run_step_parity(w, gt, ot, b, g.standard_normal((bags, dim)).astype(np.float32), 0)
+    gt.check()
+    gt.close()
+
+
+@pytest.mark.parametrize("n", [1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("mode,pad", [(W.NONE, 50), (W.TAIL, 100), (W.NONE, 200), (W.TAIL, 300)])
+def test_list_limit_of_the_padded_copy(n, mode, pad):
+    """The pad lengths take 1, 2, 4 and 8 positions per lane group (64 groups per block of dim 16); many bags are
+    longer than the pad, so ids on both sides of the window have no gradient row."""
+    print("padded edges", n, mode, pad, flush=True)
+    w = W.workload(0)
+    w.mode, w.pad_len, w.capacity_slots, w.block_rows = mode, pad, 1 << 18, 1 << 16
+    g = np.random.default_rng(n + pad)
+    gt, ot = P.gpu_table(w), P.oracle_table(w)
+    bags = n // pad
+    off = np.concatenate([[0], np.sort(g.integers(0, n + 1, size=bags - 1)), [n]]).astype(np.int64)
+    b = W.Batch(values=_ids(n, g), offsets=off, n_features=1, batch=bags)
+    P.run_step_parity(w, gt, ot, b, W.make_grad(w, b, 0), 0)
     gt.check()
     gt.close()
 

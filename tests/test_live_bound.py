@@ -119,29 +119,30 @@ def test_bound_never_below_the_live_count(lb, seed):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [6000, 20000])
+@pytest.mark.parametrize("n", [6000, 2000000])
 def test_queued_calls_do_not_drain_the_stream(n):
-    """A table with room for one more batch but not for two: a call behind a queued one waits for that one's published
-    count, not for the work queued behind it."""
-    t = R.Table(8, R.F32, R.ADAGRAD, capacity_slots=1 << 16, max_load=0.5, block_rows=1 << 14, seed=3)
-    live = (1 << 15) - n - 1000  # + n <= the limit of 2^15 keys, + 2 n above it
-    for part in torch.arange(live, device="cuda").split(4096):
+    """A call that only fits once the queued call before it (2M known keys) has published its count waits for that
+    count, not for the work queued behind that call."""
+    ahead = 2000000
+    t = R.Table(8, R.F32, R.ADAGRAD, capacity_slots=1 << 23, max_load=0.5, block_rows=1 << 20, seed=3)
+    limit = 1 << 22
+    live = limit - ahead - 3000  # the queued call fits, n more ids beside its 2M do not
+    known = torch.arange(live, device="cuda")
+    t.reserve(limit)
+    for part in known.split(1 << 20):
         t.find_or_insert(part)
-    keys = torch.arange(n, device="cuda") % live
-    t.reserve(1 << 15)
-    assert t.size() == live and t.capacity() == 1 << 16
-    x = torch.randn(4096, 4096, device="cuda")
-    torch.mm(x, x)
+    assert t.size() == live and t.capacity() == 1 << 23
+    x = torch.randn(16384, 16384, device="cuda")
+    y = torch.mm(x, x)
     for _ in range(3):
         torch.cuda.synchronize()
-        t.find_or_insert(keys)
-        for _ in range(200):
-            torch.mm(x, x)
+        t.find_or_insert(known[:ahead])
+        torch.mm(x, x, out=y)  # tens of milliseconds
         behind = torch.cuda.Event()
         behind.record()
-        rows, nins = t.find_or_insert(keys)
+        rows, nins = t.find_or_insert(known[:n])
         assert not behind.query(), "the call waited for the work queued before it"
         assert int(nins.item()) == 0 and int(rows.min().item()) >= 0
-    assert t.capacity() == 1 << 16
+    assert t.capacity() == 1 << 23
     t.check()
     t.close()
