@@ -103,7 +103,7 @@ Layout make_layout(int64_t n, int dim) {
   return L;
 }
 
-Work make_work(void* base, const Layout& L, int dim) {
+Work make_work(void* base, const Layout& L, int dim, bool list) {
   uint8_t* b = static_cast<uint8_t*>(base);
   Work w;
   w.occ_word = reinterpret_cast<uint32_t*>(b + L.occ_word);
@@ -135,6 +135,7 @@ Work make_work(void* base, const Layout& L, int dim) {
   w.gpart = reinterpret_cast<float*>(b + L.gpart);
   w.ntiles = L.ntiles;
   w.maxu = max_units(dim);
+  w.list = list;
   w.g = L.g;
   return w;
 }
@@ -275,6 +276,7 @@ struct rs_table {
   int rowscalar() const { return d.optimizer == RS_ADAGRAD_ROWWISE || d.optimizer == RS_ADAM_ROWWISE ? 1 : 0; }
   int state_elems() const { return nstate() * d.dim + rowscalar(); }
   int wbytes() const { return d.row_dtype == RS_BF16 ? 2 : 4; }
+  bool list_in_pool(int64_t n, int64_t bags) const { return rs::list_in_pool(n, bags, static_cast<int64_t>(d.dim) * wbytes()); }
 
   TableDev dev() const {
     TableDev t;
@@ -514,7 +516,7 @@ rs_status dedup_and_insert(rs_table* t, const int64_t* values, int64_t n, const 
   } else {
     t->live.enqueued(n, t->live.bound + n);
   }
-  RS_HIP(launch_compact_insert(values, n, t->dev(), w, occ_lists, t->h_pin, tag, t->ev(RS_K_COMPACT_INSERT),
+  RS_HIP(launch_compact_insert(n, t->dev(), w, occ_lists, t->h_pin, tag, t->ev(RS_K_COMPACT_INSERT),
                                t->ev(RS_K_INIT_ROWS), t->ev(RS_K_OCC), s));
   if (occ_lists && small_batch(n)) RS_HIP(launch_clear_counts(w, n, s));
   if (!occ_lists) RS_HIP(launch_map_rows(w, n, rows_out, n_inserted, s));
@@ -555,8 +557,8 @@ rs_status check_ctx(const rs_table* t, const rs_ctx* c) {
   return RS_OK;
 }
 
-Work ctx_work(const rs_ctx* c) {
-  Work w = make_work(c->workspace, make_layout(c->n, c->dim), c->dim);
+Work ctx_work(const rs_table* t, const rs_ctx* c) {
+  Work w = make_work(c->workspace, make_layout(c->n, c->dim), c->dim, t->list_in_pool(c->n, c->bags));
   w.offsets = c->offsets;
   return w;
 }
@@ -799,7 +801,7 @@ rs_status ht_find_or_insert(rs_table* t, const int64_t* keys, int64_t n, int64_t
     t->iws_bytes = t->iws ? L.total : 0;
     if (!t->iws) return fail(RS_ENOMEM, "allocation of the insert workspace failed");
   }
-  const Work w = make_work(t->iws, L, t->d.dim);
+  const Work w = make_work(t->iws, L, t->d.dim, false);
   t->clock += 1;  // one lookup call
   return dedup_and_insert(t, keys, n, w, false, rows_out, n_inserted_dev, s);
 }
@@ -985,7 +987,7 @@ rs_status lookup_prepare(rs_table* t, const int64_t* values, const int64_t* offs
     for (int64_t g = 0; g < bags; ++g)
       if (h[g + 1] < h[g]) return fail(RS_EINVAL, "offsets must be nondecreasing");
   }
-  const Work w = make_work(ctx->workspace, L, t->d.dim);
+  const Work w = make_work(ctx->workspace, L, t->d.dim, t->list_in_pool(n, bags));
   ctx->table = nullptr;  // published only once the work has been enqueued
   ctx->priv[0] = 0;      // 1: prepared, 2: pooled
   ctx->unique = w.unique;
@@ -1011,7 +1013,7 @@ rs_status lookup_pool_prepared(rs_table* t, rs_ctx* ctx, void* out, uint8_t* mas
   if (ctx->table != t || ctx->priv[0] < 1) return fail(RS_EINVAL, "context was not prepared on this table");
   if (ctx->bags > 0 && !out) return fail(RS_EINVAL, "null output");
   if (padded_mode(ctx->mode) && ctx->bags > 0 && !mask) return fail(RS_EINVAL, "null mask");
-  const Work w = ctx_work(ctx);
+  const Work w = ctx_work(t, ctx);
   RS_HIP(launch_pool(t->dev(), w, ctx->offsets, ctx->n, ctx->bags, ctx->mode, ctx->pad_len, out, mask,
                      t->ev(RS_K_POOL), static_cast<hipStream_t>(stream)));
   ctx->priv[0] = 2;
@@ -1032,7 +1034,7 @@ rs_status lookup_pool_bwd(rs_table* t, const rs_ctx* ctx, const void* grad_out, 
   rs_status st = check_ctx(t, ctx);
   if (st != RS_OK) return st;
   if (ctx->n > 0 && (!grad_out || !grad_unique)) return fail(RS_EINVAL, "null gradient");
-  const Work w = ctx_work(ctx);
+  const Work w = ctx_work(t, ctx);
   RS_HIP(launch_bwd(t->dev(), w, grad_rows(ctx), ctx->n, ctx->mode, grad_out, grad_unique, nullptr,
                     t->ev(RS_K_OCC_LIST), t->ev(RS_K_BWD_SHORT), t->ev(RS_K_BWD_LONG), static_cast<hipStream_t>(stream)));
   return RS_OK;
@@ -1045,7 +1047,7 @@ rs_status sparse_opt_step(rs_table* t, const rs_ctx* ctx, const float* grad_uniq
   if (!p) return fail(RS_EINVAL, "null optimizer parameters");
   if (ctx->n > 0 && !grad_unique) return fail(RS_EINVAL, "null grad_unique");
   const OptArgs o = make_opt(t, p);
-  const Work w = ctx_work(ctx);
+  const Work w = ctx_work(t, ctx);
   RS_HIP(launch_opt(t->dev(), w, ctx->n, grad_unique, o, t->ev(RS_K_OPT), static_cast<hipStream_t>(stream)));
   return RS_OK;
 }
@@ -1057,7 +1059,7 @@ rs_status lookup_pool_bwd_opt(rs_table* t, const rs_ctx* ctx, const void* grad_o
   if (!p) return fail(RS_EINVAL, "null optimizer parameters");
   if (ctx->n > 0 && !grad_out) return fail(RS_EINVAL, "null gradient");
   const OptArgs o = make_opt(t, p);
-  const Work w = ctx_work(ctx);
+  const Work w = ctx_work(t, ctx);
   RS_HIP(launch_bwd(t->dev(), w, grad_rows(ctx), ctx->n, ctx->mode, grad_out, nullptr, &o, t->ev(RS_K_OCC_LIST), t->ev(RS_K_BWD_SHORT),
                     t->ev(RS_K_BWD_LONG), static_cast<hipStream_t>(stream)));
   return RS_OK;

@@ -727,7 +727,7 @@ hipError_t launch_bwd(const TableDev& t, const Work& w, int64_t nref, int64_t n,
   if (n <= 0) return hipSuccess;
   {
     hipEvent_t e0 = ev_list ? ev_list[0] : nullptr, e1 = ev_list ? ev_list[1] : nullptr;
-    if (list_in_pool(n)) {  // the pool has written the list
+    if (w.list) {  // the pool has written the list
       if (e0) (void)hipEventRecord(e0, s);
       if (e1) (void)hipEventRecord(e1, s);
     } else {

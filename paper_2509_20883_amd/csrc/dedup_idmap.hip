@@ -424,7 +424,7 @@ __device__ inline int lds_insert(unsigned long long* ckey, unsigned long long e,
 
 constexpr int kRoundProbes = 64;  // probe window of a round (full windows cost as many steps per record and round)
 
-__global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w, int64_t n) {
+__global__ __launch_bounds__(kPartThreads) void k_part_dedup(TableDev t, Work w) {
   constexpr int NT = kPartThreads, S = kPartSlots, OWN = S / NT, K = kPartFast;
   constexpr int kMaxSweeps = 1 << 10;
   constexpr int BPT = (kMaxDedupBlocks + NT - 1) / NT;
@@ -828,9 +828,8 @@ __device__ inline void store_reservation(int64_t* cscal, int64_t* tscal, int64_t
 
 // Scan of the five tile-sum arrays: block c scans chunk c (kScanChunk tiles,
 // R per thread) in place and stores the chunk's totals; the last block to
-// finish (a counter, no waiting) scans the chunk totals in place, reserves
-// the rows of the new keys and publishes the live count.  A tile's prefix is
-// then bsum[a][tile] + csum[a][tile / kScanChunk].
+// finish (a counter, no waiting) scans the chunk totals in place and reserves
+// the rows of the new keys.  A tile's prefix is then bsum[a][tile] + csum[a][tile / kScanChunk].
 template <int R>
 __global__ __launch_bounds__(1024) void k_scan5(int32_t* __restrict__ bsum, int64_t nb, int64_t ntiles,
                                                 int32_t* __restrict__ csum, int64_t nch, int64_t* cscal,
@@ -958,7 +957,7 @@ hipError_t launch_dedup_keys(const int64_t* values, int64_t n, const TableDev& t
       values, n, w, reinterpret_cast<int*>(t.scal + kTErr));
   if (ev_tile && ev_tile[1]) (void)hipEventRecord(ev_tile[1], s);
   if (ev_part && ev_part[0]) (void)hipEventRecord(ev_part[0], s);
-  k_part_dedup<<<static_cast<unsigned>(g.P), kPartThreads, 0, s>>>(t, w, n);
+  k_part_dedup<<<static_cast<unsigned>(g.P), kPartThreads, 0, s>>>(t, w);
   return hipGetLastError();
 }
 
@@ -1168,7 +1167,7 @@ __device__ inline void occ_pass(const Work& w, int64_t n, uint32_t blk) {
     if (OCC) {
       *reinterpret_cast<longlong2*>(w.occ_row + i0) = make_longlong2(a[0].row, a[1].row);
       *reinterpret_cast<longlong2*>(w.occ_row + i0 + 2) = make_longlong2(a[2].row, a[3].row);
-      if (list_in_pool(n)) {  // the pool reads the positions next, and fills the list: no gradient row yet
+      if (w.list) {  // the pool reads the positions next, and fills the list: no gradient row yet
         *reinterpret_cast<int4*>(w.occ_pos + i0) = make_int4(pos[0], pos[1], pos[2], pos[3]);
         *reinterpret_cast<int4*>(w.occ_ref + i0) = make_int4(-1, -1, -1, -1);
       } else {
@@ -1181,7 +1180,7 @@ __device__ inline void occ_pass(const Work& w, int64_t n, uint32_t blk) {
       if (OCC) {
         w.occ_row[i0 + k] = a[k].row;
         w.occ_pos[i0 + k] = pos[k];
-        if (list_in_pool(n)) w.occ_ref[i0 + k] = -1;
+        if (w.list) w.occ_ref[i0 + k] = -1;
       }
     }
   }
@@ -1215,8 +1214,9 @@ __global__ __launch_bounds__(kBlock) void k_occ_init(TableDev t, Work w, int64_t
   else init_rows(t, w, b - occ_blocks - unit_blocks, gridDim.x - occ_blocks - unit_blocks);
 }
 
-hipError_t launch_compact_insert(const int64_t* values, int64_t n, const TableDev& t, const Work& w, bool occ_lists,
-                                 int64_t* h_live, int64_t tag, hipEvent_t* ev_compact, hipEvent_t* ev_init, hipEvent_t* ev_occ, hipStream_t s) {
+hipError_t launch_compact_insert(int64_t n, const TableDev& t, const Work& w, bool occ_lists, int64_t* h_live,
+                                 int64_t tag, hipEvent_t* ev_compact, hipEvent_t* ev_init, hipEvent_t* ev_occ,
+                                 hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int64_t nb = record_tiles(w.g);
   if (ev_compact && ev_compact[0]) (void)hipEventRecord(ev_compact[0], s);

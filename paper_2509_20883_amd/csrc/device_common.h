@@ -67,19 +67,6 @@ __device__ inline int block_sum(int v, int* sh) {
   return t;  // valid in thread 0
 }
 
-// 8 consecutive int32 starting at p[i0] (i0 % 8 == 0), zero past n.
-__device__ inline void load8(const int32_t* __restrict__ p, int64_t i0, int64_t n, int (&v)[8]) {
-  if (i0 + 8 <= n) {
-    const int4 a = *reinterpret_cast<const int4*>(p + i0);
-    const int4 b = *reinterpret_cast<const int4*>(p + i0 + 4);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-  } else {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = (i0 + k < n) ? p[i0 + k] : 0;
-  }
-}
-
 // E fp32 values from a 16-byte-aligned row fragment of type T (f32 or bf16).
 template <typename T, int E>
 __device__ inline void load_vals(const T* __restrict__ p, float (&v)[E]);

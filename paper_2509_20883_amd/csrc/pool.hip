@@ -7,8 +7,8 @@
 // occurrence its row (occ_row); these kernels read each occurrence's row
 // with 16-byte vector loads, one lane group of D*sizeof(row)/16 lanes per
 // row, and write the gradient row of each id (id_ref, in id order), from
-// which the backward builds its occurrence list (up to kPoolList ids
-// the list is written here).
+// which the backward builds its occurrence list (or, by list_in_pool, write
+// that list).
 //
 // A lane group handles one bag per lane and requests 16 rows of them at a
 // time, for single-id and long bags alike.
@@ -37,7 +37,7 @@ __device__ inline void record_pooled_range(const Work& w, const int64_t* offsets
 }
 
 // Gradient row of id i: kept in id order for the backward's list launch, or,
-// up to kPoolList ids, put at the id's place in the occurrence list at once
+// where the pool writes the list, put at the id's place in it at once
 // (pos: occ_pos[i], -1 for an id that takes no part).
 template <bool LIST>
 __device__ inline void write_ref(const Work& w, int64_t i, int pos, int ref) {
@@ -311,7 +311,7 @@ static hipError_t pool_dim(RS_POOL_ARGS) {
 
 template <typename WT, bool PADDED>
 hipError_t pool_part(RS_POOL_ARGS) {
-  return list_in_pool(n) ? pool_dim<WT, PADDED, true>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s)
+  return w.list ? pool_dim<WT, PADDED, true>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s)
                          : pool_dim<WT, PADDED, false>(t, w, offsets, n, bags, mode, pad_len, out, mask, e0, e1, s);
 }
 

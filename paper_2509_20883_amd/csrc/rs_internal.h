@@ -56,15 +56,28 @@ constexpr int kScanChunk = 2048;
 
 // A batch of at most kSmallIds ids runs its front end in two launches (unless
 // the table may have to grow), and its pool fills the occurrence list itself.
+// The line is what the LDS of one block holds; a step of 8192 ids takes 31 us,
+// of 8193 (the general front end) 63, of 32768 69 and of 100,000 78.
 constexpr int kSmallIds = 8192;
 __host__ __device__ inline bool small_batch(int64_t n) { return n <= kSmallIds; }
-// Up to kPoolList ids the pool stores each id's gradient row at its place in
-// the occurrence list itself: the list stays in the caches, which merge the
-// scattered 4-byte stores, and the backward's list launch falls away; of a
-// larger list every such store costs a sector of memory traffic (list launch
-// 12.7 us and pool + 6 for 0.86M ids, 13 and + 6 for 1.0M, 16 and + 13 for 1.7M).
-constexpr int64_t kPoolList = int64_t(1) << 21;
-__host__ __device__ inline bool list_in_pool(int64_t n) { return n <= kPoolList; }
+// Whether the pool stores each id's gradient row at its place in the occurrence
+// list itself, so that the backward's list launch falls away.  Its scattered
+// 4-byte stores are merged by the caches while the list stays there; of a longer
+// list, or of one that the rows read meanwhile push out, every store costs a
+// sector of memory traffic.  Steps (adagrad, us) with the list launch / in the
+// pool, bags of 10 ids on average: 16 fp32 columns, 1.0M ids 142 / 138, 2.0M 219
+// / 217; 64 columns, 0.5M 140 / 132, 1.5M 255 / 251, 1.75M 295 / 298, 2.0M 304 /
+// 314; 128 columns, 0.5M 167 / 162, 0.75M 229 / 227, 1.0M 290 / 294, 2.0M 476 /
+// 497; 256 columns, 0.5M 229 / 226, 0.75M 365 / 373; padded copy of 64 columns,
+// 1.25M 364 / 353, 2.0M 600 / 636.  So up to kListBytes of rows, except where
+// most bags hold one id: there it gains or is even up to kListIds (128 bf16
+// columns, 2.0M 835 / 781; 64 fp32, 449 / 453; 256 fp32, 1.0M 709 / 710).
+constexpr int64_t kListIds = int64_t(1) << 21;
+constexpr int64_t kListBytes = int64_t(384) << 20;
+static_assert(int64_t(kSmallIds) * 1024 <= kListBytes, "a small batch's list is always the pool's (rows: 32 to 1024 bytes)");
+inline bool list_in_pool(int64_t n, int64_t bags, int64_t row_bytes) {
+  return n <= kListIds && (2 * bags >= n || n * row_bytes <= kListBytes);
+}
 
 // Open addressing with linear probing; a lookup reads kProbeBatch
 // consecutive IDMap slots (64 bytes) per round trip.
@@ -85,6 +98,9 @@ static_assert(kUnit == 1 << kUnitLog2, "kUnit is a power of two");
 // (dim <= 16: at least 64 lane groups per block share the partial rows) take
 // more and shorter units: 1M ids of dim 16 with a key of 150,000 unit sums
 // 38 -> 19 us, finish 6 -> 8; 0.86M of dim 128 (16 groups) 67 -> 56 and 17 -> 45.
+// Steps of 1M ids with at most 1024 / 4096 units, Zipf 1.1 and 1.3: dim 8 218 /
+// 210 and 136 / 117 us, 16 172 / 170 and 128 / 117, 32 184 / 188 and 139 / 133,
+// 64 234 / 248 and 172 / 179, 128 356 / 374 and 252 / 270.
 __host__ __device__ inline int max_units(int dim) { return dim <= 16 ? 4096 : 1024; }
 __host__ __device__ inline int unit_shift(int count, int maxu) {
   int sh = 0;
@@ -278,8 +294,9 @@ struct Work {
   Seg* useg;            // [n]
   int64_t* rows;        // [n]
   int32_t* new_list;    // [n] unique id of the k-th inserted key
-  int32_t* id_ref;      // [n] gradient row of each id (written by the pool; -1: none)
-  int32_t* occ_ref;     // [n] gradient row of each position of the occurrence list
+  int32_t* id_ref;      // [n] gradient row of each id (written by the pool; -1: none; not where it writes
+                        //     occ_ref); a small batch: finished backward units of each hot key
+  int32_t* occ_ref;     // [n] gradient row of each position of the occurrence list (-1: none)
   const int64_t* offsets;  // the forward's bag offsets (mean pooling: the backward's 1 / bag length)
   int32_t* long_u;      // [n/kLong + 1] unique id of each hot key
   int32_t* long_start;  // [n/kLong + 1] first backward unit of each hot key
@@ -289,6 +306,7 @@ struct Work {
   int64_t* scal;        // [kCScalars]
   float* gpart;         // [(2n/kUnit + 2) * D] partial gradient row of each backward unit
   int maxu;             // most backward units of a key (max_units)
+  bool list;            // the pool writes the occurrence list (list_in_pool)
   int64_t ntiles;       // record tiles (kRankTile records of one dedup block each; bsum stride)
   FrontGeom g;
 };
@@ -341,8 +359,9 @@ hipError_t launch_ids_partition(const int64_t* values, int64_t n, int G, uint64_
 // list position and the hot keys' backward units.  Also stores (tag << 48) |
 // (live rows after the call) to h_live (pinned host memory; may be null), so
 // the host can refresh its bound on the live count without a copy or an event.
-hipError_t launch_compact_insert(const int64_t* values, int64_t n, const TableDev& t, const Work& w, bool occ_lists,
-                                 int64_t* h_live, int64_t tag, hipEvent_t* ev_compact, hipEvent_t* ev_init, hipEvent_t* ev_occ, hipStream_t s);
+hipError_t launch_compact_insert(int64_t n, const TableDev& t, const Work& w, bool occ_lists, int64_t* h_live,
+                                 int64_t tag, hipEvent_t* ev_compact, hipEvent_t* ev_init, hipEvent_t* ev_occ,
+                                 hipStream_t s);
 // A small batch (0 < n <= kSmallIds) on a table with room for n new keys: the
 // whole front end up to and including the new rows (publishes the live count
 // as launch_compact_insert).  occ_lists: a forward; else rows_out [n] and

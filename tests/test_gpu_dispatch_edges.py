@@ -1,7 +1,8 @@
 """Both sides of the dispatch rules on batch size, against the oracle.
 
-The occurrence list is written by the pool (pooled or padded) up to 2^21 ids and
-by a launch of the backward above; a hot key has at most 4096 units in rows of dim <= 16 and
+The occurrence list is written by the pool (pooled or padded) up to 2^21 ids
+and, unless most bags hold one id, 384 MiB of rows, and by a launch of the
+backward above; a hot key has at most 4096 units in rows of dim <= 16 and
 1024 in wider ones (a key of 140,000 occurrences passes both limits); the ids
 partition keeps at most 2048 owner blocks (above 2^21 ids a block takes several
 record tiles) and scans up to 8192, up to 16384, or more counts.  Integers
@@ -37,6 +38,23 @@ def test_list_and_unit_limits(n, dim, mode):
     bags = n // 12
     off = np.concatenate([[0], np.sort(g.integers(0, n + 1, size=bags - 1)), [n]]).astype(np.int64)
     b = W.Batch(values=_ids(n, g), offsets=off, n_features=1, batch=bags)
+    P.run_step_parity(w, gt, ot, b, g.standard_normal((bags, dim)).astype(np.float32), 0)
+    gt.check()
+    gt.close()
+
+
+@pytest.mark.parametrize("dim,dtype,n", [(256, W.F32, 393216), (256, W.F32, 393217), (128, W.BF16, (3 << 19) + 1)])
+@pytest.mark.parametrize("ids_per_bag", [1, 2, 2.001, 12])
+def test_list_limit_of_wide_rows(dim, dtype, n, ids_per_bag):
+    """384 MiB of rows and one more; bags of up to two ids on average keep the list in the pool."""
+    print("wide rows", dim, dtype, n, ids_per_bag, flush=True)
+    w = W.workload(0)
+    w.mode, w.dim, w.row_dtype, w.capacity_slots, w.block_rows = W.SUM, dim, dtype, 1 << 18, 1 << 16
+    g = np.random.default_rng(n + dim)
+    gt, ot = P.gpu_table(w), P.oracle_table(w)
+    bags = int(np.ceil(n / ids_per_bag))
+    off = np.concatenate([[0], np.sort(g.integers(0, n + 1, size=bags - 1)), [n]]).astype(np.int64)
+    b = W.Batch(values=g.integers(0, 30000, size=n), offsets=off, n_features=1, batch=bags)
     P.run_step_parity(w, gt, ot, b, g.standard_normal((bags, dim)).astype(np.float32), 0)
     gt.check()
     gt.close()
