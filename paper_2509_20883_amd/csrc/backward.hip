@@ -587,14 +587,56 @@ hipError_t bwd_part(RS_BWD_ARGS) {
   return bwd_dim<WT, float, 0, FUSED>(t, w, nref, n, mode, grad, gu, o, es, el, s);
 }
 
+// ---------------------------------------------------------------------------
+// optimizer from a written grad_unique (the two-call path)
+// ---------------------------------------------------------------------------
+
+template <typename WT, int LANES>
+__global__ __launch_bounds__(kBlock) void k_opt(TableDev t, Work w, const float* __restrict__ grad_unique, OptArgs o) {
+  constexpr int E = 4;
+  constexpr int GPB = kBlock / LANES;
+  constexpr int D = LANES * E;
+  const int lane = threadIdx.x % LANES;
+  const int grp = threadIdx.x / LANES;
+  const int64_t U = w.scal[kCU];
+  for (int64_t u = static_cast<int64_t>(blockIdx.x) * GPB + grp; u < U; u += static_cast<int64_t>(gridDim.x) * GPB) {
+    const int64_t r = w.useg[u].row;
+    if (r < 0) continue;
+    uint8_t* rp = t.store.row(r);
+    RowFrag<WT, E> fr;
+    fr.load(rp, lane, D, t.nstate, t.rowscalar);
+    float g[E];
+    load_vals<float, E>(grad_unique + u * D + lane * E, g);
+    fr.template update_store<LANES>(rp, lane, D, g, o);
+  }
+}
+
+#define RS_OPT_ARGS const TableDev &t, const Work &w, int64_t n, const float *gu, const OptArgs &o, hipStream_t s
+
+template <typename WT>
+hipError_t opt_dim(RS_OPT_ARGS) {
+  switch (t.dim / 4) {
+    case 2: k_opt<WT, 2><<<grid_for(n, kBlock / 2, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
+    case 4: k_opt<WT, 4><<<grid_for(n, kBlock / 4, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
+    case 8: k_opt<WT, 8><<<grid_for(n, kBlock / 8, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
+    case 16: k_opt<WT, 16><<<grid_for(n, kBlock / 16, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
+    case 32: k_opt<WT, 32><<<grid_for(n, kBlock / 32, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
+    case 64: k_opt<WT, 64><<<grid_for(n, kBlock / 64, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 #if RS_PART == 1
 template hipError_t bwd_part<float, true>(RS_BWD_ARGS);
 #elif RS_PART == 2
 template hipError_t bwd_part<float, false>(RS_BWD_ARGS);
+template hipError_t opt_dim<float>(RS_OPT_ARGS);
 #elif RS_PART == 3
 template hipError_t bwd_part<uint16_t, true>(RS_BWD_ARGS);
 #elif RS_PART == 4
 template hipError_t bwd_part<uint16_t, false>(RS_BWD_ARGS);
+template hipError_t opt_dim<uint16_t>(RS_OPT_ARGS);
 #endif
 
 #if RS_PART == 0
@@ -602,6 +644,8 @@ extern template hipError_t bwd_part<float, true>(RS_BWD_ARGS);
 extern template hipError_t bwd_part<float, false>(RS_BWD_ARGS);
 extern template hipError_t bwd_part<uint16_t, true>(RS_BWD_ARGS);
 extern template hipError_t bwd_part<uint16_t, false>(RS_BWD_ARGS);
+extern template hipError_t opt_dim<float>(RS_OPT_ARGS);
+extern template hipError_t opt_dim<uint16_t>(RS_OPT_ARGS);
 
 template <typename GT, int LANES, int MODE>
 void units_launch(const Work& w, uint32_t nref, int64_t n, const GT* grad, hipEvent_t start, hipStream_t s) {
@@ -742,45 +786,6 @@ hipError_t launch_bwd(const TableDev& t, const Work& w, int64_t nref, int64_t n,
                        : bwd_part<float, true>(t, w, nr, n, mode, grad, grad_unique, o, ev_short, ev_long, s);
   return t.row_dtype ? bwd_part<uint16_t, false>(t, w, nr, n, mode, grad, grad_unique, o, ev_short, ev_long, s)
                      : bwd_part<float, false>(t, w, nr, n, mode, grad, grad_unique, o, ev_short, ev_long, s);
-}
-
-// ---------------------------------------------------------------------------
-// optimizer from a written grad_unique (the two-call path)
-// ---------------------------------------------------------------------------
-
-template <typename WT, int LANES>
-__global__ __launch_bounds__(kBlock) void k_opt(TableDev t, Work w, const float* __restrict__ grad_unique, OptArgs o) {
-  constexpr int E = 4;
-  constexpr int GPB = kBlock / LANES;
-  constexpr int D = LANES * E;
-  const int lane = threadIdx.x % LANES;
-  const int grp = threadIdx.x / LANES;
-  const int64_t U = w.scal[kCU];
-  for (int64_t u = static_cast<int64_t>(blockIdx.x) * GPB + grp; u < U; u += static_cast<int64_t>(gridDim.x) * GPB) {
-    const int64_t r = w.useg[u].row;
-    if (r < 0) continue;
-    uint8_t* rp = t.store.row(r);
-    RowFrag<WT, E> fr;
-    fr.load(rp, lane, D, t.nstate, t.rowscalar);
-    float g[E];
-    load_vals<float, E>(grad_unique + u * D + lane * E, g);
-    fr.template update_store<LANES>(rp, lane, D, g, o);
-  }
-}
-
-template <typename WT>
-static hipError_t opt_dim(const TableDev& t, const Work& w, int64_t n, const float* gu, const OptArgs& o,
-                          hipStream_t s) {
-  switch (t.dim / 4) {
-    case 2: k_opt<WT, 2><<<grid_for(n, kBlock / 2, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
-    case 4: k_opt<WT, 4><<<grid_for(n, kBlock / 4, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
-    case 8: k_opt<WT, 8><<<grid_for(n, kBlock / 8, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
-    case 16: k_opt<WT, 16><<<grid_for(n, kBlock / 16, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
-    case 32: k_opt<WT, 32><<<grid_for(n, kBlock / 32, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
-    case 64: k_opt<WT, 64><<<grid_for(n, kBlock / 64, kResident), kBlock, 0, s>>>(t, w, gu, o); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
 }
 
 hipError_t launch_opt(const TableDev& t, const Work& w, int64_t n, const float* grad_unique, const OptArgs& opt,
