@@ -214,7 +214,7 @@ def kernels_from(a):
         m = defaultdict(list)
         for r in _counter_rows(d):
             m[_kname(r)].append((int(r["Dispatch_Id"]), float(r["Counter_Value"]) * 1024))
-        return {k: max(v)[1] for k, v in m.items()}
+        return _drop_setup_only({k: max(v) for k, v in m.items()})
 
     fs, ws = calib(cfdir), calib(cwdir)
     F, Wr = last(fdir), last(wdir)
@@ -287,6 +287,13 @@ def copy_calibration():
     print(json.dumps({"copy_bytes_read": n, "copy_bytes_written": n, "ms": ms, "GBps": 2 * n / (ms * 1e-3) / 1e9}))
 
 
+def _drop_setup_only(last):
+    """{kernel: (last dispatch, value)} -> {kernel: value} without the kernels that only the set-up ran (the scratch
+    table's small batch): their last dispatch is before the last step's first kernel."""
+    first = last.get("rs::k_tile_dedup<1024>", (-1, None))[0]
+    return {k: v for k, (d, v) in last.items() if d >= first}
+
+
 def _counter_rows(d: str):
     """Rows of the counter_collection CSV under a rocprofv3 output directory."""
     import csv
@@ -343,7 +350,7 @@ def traffic_from(a):
         for r in _counter_rows(d):
             name = r["Kernel_Name"].split("(")[0].replace("void ", "").strip()
             by[name].append((int(r["Dispatch_Id"]), float(r["Counter_Value"])))
-        return {k: max(v)[1] * 1024 for k, v in by.items()}
+        return {k: v * 1024 for k, v in _drop_setup_only({k: max(v) for k, v in by.items()}).items()}
 
     F, Wr = last(fdir), last(wdir)
     wl = profile_label(a)
@@ -446,9 +453,10 @@ def counters_from(a):
     for r in rows:
         k, d = _kname(r), int(r["Dispatch_Id"])
         last[k] = max(last.get(k, -1), d)
+    kept = _drop_setup_only({k: (d, d) for k, d in last.items()})
     for r in rows:
         k = _kname(r)
-        if int(r["Dispatch_Id"]) == last[k]:
+        if k in kept and int(r["Dispatch_Id"]) == last[k]:
             vals[k][r["Counter_Name"]] = float(r["Counter_Value"])
     lines = [f"# L2 hits and atomics per launch: {wl}", "", "Command (MI355X, repository root copied to `<repo>`):",
              "", "```", a.traffic_cmd or "(command not recorded)", "```", "",

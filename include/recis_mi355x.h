@@ -186,7 +186,8 @@ rs_status ht_destroy(rs_table* t);
  * to nearest even) with u_j = (splitmix64 output j+1 from state
  * mix(key ^ mix(seed))) >> 40 times 2^-24; optimizer state = 0.
  * n_inserted_dev: device int64 scalar receiving the number inserted (may be NULL).
- * May synchronize the stream when the table has to grow. */
+ * May wait for earlier calls' counts, and synchronize the stream, when the
+ * table may have to grow. */
 rs_status ht_find_or_insert(rs_table* t, const int64_t* keys, int64_t n, int64_t* rows_out,
                             int64_t* n_inserted_dev, rs_stream stream);
 
@@ -315,9 +316,10 @@ rs_status lookup_pool_prepared(rs_table* t, rs_ctx* ctx, void* out, uint8_t* mas
  * grad_unique [n, D] fp32: row u (< U) receives
  *   sum over occurrences i of unique u of scale(bag(i)) * grad_out[bag(i)]
  * (scale 1 for sum, 1/len for mean; padded: grad_out[g][t] for the id copied
- * to slot t; ids that were not copied contribute nothing).  Its first launch
- * lays out the per-key occurrence list from the gradient row of each id that
- * the ctx's pool wrote, so the pool precedes it; ids outside
+ * to slot t; ids that were not copied contribute nothing).  The per-key
+ * occurrence list comes from the gradient row of each id, which the ctx's pool
+ * writes (into the list itself, or for the backward's first launch to lay it
+ * out), so the pool precedes it; ids outside
  * [offsets[0], offsets[bags]) contribute nothing.  The order of a key's
  * occurrences in that list (so the fp32 summation order) is not fixed from
  * run to run: sums may differ in their last bits between runs. */
@@ -420,6 +422,13 @@ rs_status fused_mod(const int64_t* values, int64_t n, const int64_t* col_offsets
  * timestamped by the dispatch (the kernel's own execution; for RS_K_BWD_LONG
  * from the unit sums' start to the finish's end); for the other kernels they
  * are recorded on the call's stream immediately before / after the launch.
+ * A call that needs no launch for a kernel records its two events one after
+ * the other (a few microseconds apart): RS_K_OCC_LIST where the pool writes
+ * the list (up to 2^21 ids, see lookup_pool_bwd), and in a batch of at most
+ * 8192 ids on a table with room RS_K_PARTITION, RS_K_INIT_ROWS and RS_K_OCC
+ * (its two front-end launches are timed as RS_K_TILE_DEDUP and
+ * RS_K_COMPACT_INSERT) and RS_K_BWD_LONG (its one backward launch, hot keys
+ * and all, is timed as RS_K_BWD_SHORT).
  * The events must exist (created, e.g. recorded once) before the call that
  * uses them.  For measurement only. */
 typedef enum {
@@ -435,8 +444,9 @@ typedef enum {
   RS_K_OPT = 7,            /* optimizer from grad_unique (two-call path)        */
   RS_K_OCC = 8,            /* per-occurrence rows, list positions, inverse; the
                               same launch writes the rows of inserted keys      */
-  RS_K_OCC_LIST = 9,       /* the backward's first launch: the occurrence list
-                              (each position's gradient row)                    */
+  RS_K_OCC_LIST = 9,       /* the backward's first launch, where the pool does
+                              not write it: the occurrence list (each
+                              position's gradient row)                          */
   RS_K_COUNT = 10
 } rs_kernel_id;
 rs_status rs_set_kernel_events(rs_table* t, int32_t kernel, void* start_event, void* stop_event);

@@ -940,7 +940,8 @@ FrontGeom front_geom(int64_t n) {
   g.P = 1;
   g.logP = 0;
   // about 4096 ids (some 1500-2000 records) per partition: the partitions of
-  // a batch up to ~3M ids are all resident at once (3 blocks per CU)
+  // a batch up to ~3M ids are all resident at once (3 blocks per CU by their
+  // registers; their 40 KB of LDS would admit four)
   while (g.P < kMaxParts && static_cast<int64_t>(g.P) * 4096 < n1) {
     g.P <<= 1;
     ++g.logP;

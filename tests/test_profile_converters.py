@@ -142,3 +142,9 @@ def test_kernel_table_joins_time_traffic_and_ceiling(tmp_path, out):
     # (4.096 + 1.024) GB in 1 ms = 5120 GB/s, 80% of the probe's 6400
     assert f"| `{kern}` | 1000.0 | 4096.0 | 1024.0 | 5120 | read-modify-write of random 768-byte rows (+ index) " \
            f"| 6400 | 80 |" in md
+
+
+def test_kernels_of_the_set_up_alone_are_left_out():
+    last = {"rs::k_bwd_small<float>": (7, 1.0), "rs::k_tile_dedup<1024>": (20, 2.0), "rs::k_pool<float>": (24, 3.0)}
+    assert B._drop_setup_only(last) == {"rs::k_tile_dedup<1024>": 2.0, "rs::k_pool<float>": 3.0}
+    assert B._drop_setup_only({"rs::k_bucketize": (3, 1.0)}) == {"rs::k_bucketize": 1.0}
