@@ -289,7 +289,7 @@ def copy_calibration():
 
 def _drop_setup_only(last):
     """{kernel: (last dispatch, value)} -> {kernel: value} without the kernels that only the set-up ran (the scratch
-    table's small batch): their last dispatch is before the last step's first kernel."""
+    table's step): their last dispatch is before the last step's first kernel."""
     first = last.get("rs::k_tile_dedup<1024>", (-1, None))[0]
     return {k: v for k, (d, v) in last.items() if d >= first}
 
@@ -418,7 +418,7 @@ def trace_from(a):
         by[_kname(r)].append((int(r["Dispatch_Id"]), (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
     step = {k: v for k, v in by.items() if k.startswith("rs::") and "probe" not in k and "rehash" not in k
             and "map_rows" not in k and "k_occ_init<false>" not in k and "rereserve" not in k}
-    if getattr(a, "evict_age", -1) < 0:  # a kernel of the set-up alone (the scratch table's small batch) is no part of a step
+    if getattr(a, "evict_age", -1) < 0:  # a kernel of the set-up alone (the scratch table's step) is no part of a step
         step = {k: v for k, v in step.items() if len(v) >= a.steps}
     how = (f"--op {a.op} --shards {a.shards or 8}" if a.op == "ids-partition" else
            f"--op {a.op}" if a.op != "step" else f"--workload {a.workload}")
@@ -980,16 +980,18 @@ def main():
 
     side = torch.cuda.Stream(device=dev)  # default priority
 
-    # a kernel's code object is loaded at its first launch: one step of 1024
-    # bags spread over the first batch (the same mix of bag lengths, so the
-    # same kernel variants) on a small scratch table of the same kind loads
-    # every kernel of the step, so the first warm-up step is no cold start
+    # a code object is loaded at the first launch from it: one step of bags
+    # spread over the first batch (the same mix of bag lengths), 1024 of them
+    # or about 16384 ids (past the small batches' own kernels), on a small
+    # scratch table of the same kind loads the step's code objects, so the
+    # first warm-up step is no cold start
     scratch = R.Table(w.dim, w.row_dtype, w.opt, w.init_lo, w.init_hi, w.table_seed, 1 << 17, w.max_load,
                       w.block_rows, auto_grow=True, evictable=evictable)
     try:
         v0, o0, _, g0 = batches[0]
         oh = o0.cpu().numpy()
-        pick = np.unique(np.linspace(0, g0 - 1, num=min(g0, 1024)).round().astype(np.int64))
+        some = min(g0, max(1024, int(16384 * g0 / max(int(oh[-1]), 1))))
+        pick = np.unique(np.linspace(0, g0 - 1, num=some).round().astype(np.int64))
         lens = oh[pick + 1] - oh[pick]
         so_h = np.zeros(pick.size + 1, dtype=np.int64)
         np.cumsum(lens, out=so_h[1:])
